@@ -394,8 +394,8 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
         if (VEC && gj + 8 <= n) {
             __builtin_nontemporal_store(o, reinterpret_cast<nu4 *>(dst));
         } else {
-            const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
-            const uint16_t *e8 = reinterpret_cast<const uint16_t *>(ow);
+            uint16_t e8[8];   // (a copy, not a pointer cast: read as another type, the words are not the compiler's to keep)
+            __builtin_memcpy(e8, &o, sizeof(e8));
             for (int e = 0; e < 8 && gj + e < n; ++e)
                 dst[e] = e8[e];
         }

@@ -292,7 +292,9 @@ __global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob<GT>>
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 h[e] = f32_to_bf16(v[e]);
-            *reinterpret_cast<uint4 *>(M16 + tile_at(i, j0, ntc)) = *reinterpret_cast<const uint4 *>(h);
+            uint4 hv;
+            __builtin_memcpy(&hv, h, sizeof(hv));
+            *reinterpret_cast<uint4 *>(M16 + tile_at(i, j0, ntc)) = hv;
         } else {
             for (int e = 0; e < 8 && j0 + e < n; ++e) {
                 float x = mr[e];
@@ -1133,7 +1135,8 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const Batch<SumJob> jb)
         // squares of bf16 are exact in fp32; the V of one chunk are added in fp32
         for (int64_t c = start; c < J.count / V; c += stride) {
             const uint4 raw = reinterpret_cast<const uint4 *>(G)[c];
-            const GT *e = reinterpret_cast<const GT *>(&raw);
+            GT e[V];
+            __builtin_memcpy(e, &raw, sizeof(e));
             float s = 0.f;
 #pragma unroll
             for (int i = 0; i < V; ++i) {
@@ -1417,7 +1420,7 @@ __global__ __launch_bounds__(256) void blend16_kernel(const Batch<BlendJob<uint1
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     e8[e] = (gj + e < n) ? src[e] : uint16_t(0);
-                v = *reinterpret_cast<const uint4 *>(e8);
+                __builtin_memcpy(&v, e8, sizeof(v));
             }
         }
         gr[u] = v;
@@ -1526,7 +1529,8 @@ __global__ __launch_bounds__(256) void blend16_kernel(const Batch<BlendJob<uint1
         if (VEC && gj + 8 <= n) {
             *reinterpret_cast<uint4 *>(dst) = v;
         } else {
-            const uint16_t *e8 = reinterpret_cast<const uint16_t *>(&v);
+            uint16_t e8[8];
+            __builtin_memcpy(e8, &v, sizeof(e8));
             for (int e = 0; e < 8 && gj + e < n; ++e)
                 dst[e] = e8[e];
         }

@@ -80,6 +80,23 @@ def test_correct_ragged_shapes(pk, dtype, m, n, r):
     assert osp.rel_fro(_np(out), ref) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("m,n,r", [(130, 260, 64), (257, 1003, 50), (129, 515, 128), (200, 333, 190), (300, 1001, 24),
+                                   (140, 452, 80)])
+def test_correct_stores_widths_that_are_no_multiple_of_8(pk, m, n, r):
+    """bf16 rows that are not 16-byte aligned take the element-wise stores of
+    the blend at every padded rank; the output starts as NaN, so an element
+    that is not stored shows."""
+    U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=m + n + r)
+    G = (((U * 0.5) @ V.T) + 0.02 * workloads.gaussian((m, n), seed=4).double()).to(torch.bfloat16)
+    d = osp.filter_weights(s.numpy(), 0.7)
+    ref = osp.correct(_np(G), U.numpy(), d, V.numpy(), 0.3)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    pk.sc_correct(G.cuda(), U.float().cuda(), torch.tensor(d, dtype=torch.float32).cuda(), V.float().cuda(), 0.3,
+                  out=out)
+    torch.cuda.synchronize()
+    assert osp.rel_fro(_np(out), ref) <= TOL[torch.bfloat16]
+
+
 def test_correct_in_place_and_alpha_one(pk):
     m, n, r = 512, 384, 16
     U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=1)
