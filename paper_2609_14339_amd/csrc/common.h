@@ -90,6 +90,37 @@ __device__ __forceinline__ float blend_step(float g, float p, float alpha, float
     return __builtin_fmaf(alpha, g, oma * p);
 }
 
+// Sum, in order, of `splits` >= 1 partials `ss` floats apart (16-byte aligned).
+// The loads of four partials are issued before the first is added: one at a
+// time, each addition waits a memory latency (the Gram kernel of six 1B-class
+// blocks of 48 columns, 4 to 16 partials: 13.7 us that way, 11.1 so).
+__device__ __forceinline__ float4 sum_partials(const float *p, int64_t ss, int splits)
+{
+    float4 v = *reinterpret_cast<const float4 *>(p);
+    int q = 1;
+    for (; q + 4 <= splits; q += 4) {
+        float4 x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            x[e] = *reinterpret_cast<const float4 *>(p + (q + e) * ss);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v.x += x[e].x;
+            v.y += x[e].y;
+            v.z += x[e].z;
+            v.w += x[e].w;
+        }
+    }
+    for (; q < splits; ++q) {
+        const float4 x = *reinterpret_cast<const float4 *>(p + q * ss);
+        v.x += x.x;
+        v.y += x.y;
+        v.z += x.z;
+        v.w += x.w;
+    }
+    return v;
+}
+
 // bf16 <-> fp32 on bit patterns.
 __device__ __forceinline__ float bf16_to_f32(uint16_t h)
 {

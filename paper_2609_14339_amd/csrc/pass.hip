@@ -19,6 +19,7 @@
 #include <cstdlib>
 #include <functional>
 #include <map>
+#include <limits>
 #include <mutex>
 
 namespace acsc {
@@ -418,9 +419,15 @@ struct SegBatch {
 // the MFMA's power draw, not HBM, sets their pace: covering 144 columns with
 // 16-wide tiles (rather than padding to 160 for 32x32 tiles) takes 8% less
 // time, and needs fewer fragment reads than 32x32 tiles plus a 16-wide one.
+// Up to 64 columns two workgroups share a CU, with two stages each: the same
+// bytes in flight per CU, but one workgroup's start, end and barriers hide
+// under the other's stream.
+constexpr int kTwoPerCuNP = 64;
+constexpr int waves_per_simd(int NT) { return NT * 16 <= kTwoPerCuNP ? 4 : 2; }
+
 template <bool TRANS, int NT, int S>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pass_dma_kernel(const SegBatch sb,
-                                                                                                  int np)
+__global__ __launch_bounds__(512)
+    __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT), waves_per_simd(NT)))) void pass_dma_kernel(const SegBatch sb, int np)
 {
     const int wg = static_cast<int>(blockIdx.x);
     int si = 0;
@@ -691,8 +698,9 @@ void launch_scalar(const char *tag, const std::vector<Job> &jobs, int gx, int np
 template <bool TRANS, int NTK>
 void launch_segs(const char *tag, const SegBatch &b, int grid, int np, hipStream_t st)
 {
-    // three LDS stages while they fit in 160 KiB, else two
-    constexpr int S = (3 * (256 * 128 + NTK * 16 * 128) <= 160 * 1024) ? 3 : 2;
+    // two workgroups per CU with two LDS stages each; else three stages while
+    // they fit in 160 KiB, else two
+    constexpr int S = NTK * 16 > kTwoPerCuNP && 3 * (256 * 128 + NTK * 16 * 128) <= 160 * 1024 ? 3 : 2;
     auto kern = pass_dma_kernel<TRANS, NTK, S>;
     ACSC_LAUNCH(tag, kern, dim3(grid), dim3(512), 0, st, b, np);
 }
@@ -1139,6 +1147,84 @@ void ema_launch(const char *tag, const EmaBatch &b, int grid, int np, float a, f
     ACSC_LAUNCH(tag, ema_pass_kernel<NT>, dim3(grid), dim3(512), 0, st, b, np, a, b_coef, spin);
 }
 
+// k pieces per row block for a batch whose row blocks do not fill the GPU.
+// One pass workgroup fills a CU, so the pass takes as long as the CU with the
+// most steps: a common piece length serves a batch that mixes row lengths
+// better than one split count for every job (with 2048- and 8192-deep rows
+// cut in four, the CUs of the long rows work four times as long as the
+// others).  The lengths between "one round of equal pieces" and whole rows
+// are tried on the simulated dispatch; a piece costs kPieceOver steps more
+// for its empty pipeline and np / 32 for the partial it stores (a step is 32
+// KiB of the stream per CU).  Measured on the six matrices of a 1B-class
+// layer at 48 columns: 32-34 us per pass with one power-of-two split count for the
+// batch, 25-26 us so; on the four of an 8B-class layer at 80 columns 68-72
+// and 55-60 us.
+constexpr int kPieceOver = 4;
+
+struct SplitShape {
+    int nrb, K, cap;   // row blocks, depth, most pieces
+};
+
+std::vector<int> choose_splits(const std::vector<SplitShape> &js, int np)
+{
+    int xcds = 8, cpx = 32;
+    device_cus(xcds, cpx);
+    const int64_t cus = static_cast<int64_t>(xcds) * cpx;
+    if (np <= kTwoPerCuNP)
+        cpx *= 2;
+    std::vector<int64_t> key{xcds, cpx, np};
+    int64_t blocks = 0, total = 0, longest = 1;
+    for (const SplitShape &j : js) {
+        const int64_t steps = cdiv(j.K, kBK);
+        blocks += j.nrb;
+        total += j.nrb * steps;
+        longest = std::max(longest, steps);
+        key.insert(key.end(), {j.nrb, j.K, j.cap});
+    }
+    std::vector<int> best(js.size(), 1);
+    if (blocks >= cus)
+        return best;
+    static std::mutex mu;
+    static std::map<std::vector<int64_t>, std::vector<int>> cache;
+    {
+        std::lock_guard<std::mutex> g(mu);
+        auto it = cache.find(key);
+        if (it != cache.end())
+            return it->second;
+    }
+    int64_t best_cost = std::numeric_limits<int64_t>::max();
+    for (int64_t len = std::max<int64_t>(1, cdiv(total, static_cast<int64_t>(xcds) * cpx)); ; len = std::max(len + 1, len + len / 12)) {
+        std::vector<int> sp;
+        std::vector<int> cost;
+        bool split = false;
+        for (const SplitShape &j : js) {
+            const int64_t steps = cdiv(j.K, kBK);
+            const int64_t s0 = std::max<int64_t>(1, std::min<int64_t>(j.cap, cdiv(steps, len)));
+            const int64_t chunk = cdiv(steps, s0);
+            const int s = static_cast<int>(cdiv(steps, chunk));
+            sp.push_back(s);
+            split = split || s > 1;
+            cost.resize(static_cast<size_t>(round_up(static_cast<int64_t>(cost.size()), 8)), 0);
+            for (int b = 0; b < j.nrb; ++b)
+                for (int p = 0; p < s; ++p)
+                    cost.push_back(static_cast<int>(32 * (std::min<int64_t>(chunk, steps - p * chunk) + kPieceOver) +
+                                                    (s > 1 ? np : 0)));
+        }
+        const int64_t c = simulate_dispatch(cost, xcds, cpx);
+        if (c < best_cost) {
+            best_cost = c;
+            best = sp;
+        }
+        if (!split || len > longest)
+            break;
+    }
+    std::lock_guard<std::mutex> g(mu);
+    if (cache.size() >= 1024)
+        cache.clear();
+    cache.emplace(key, best);
+    return best;
+}
+
 }  // namespace
 
 int max_splits(int64_t M, int64_t K)
@@ -1150,7 +1236,45 @@ int max_splits(int64_t M, int64_t K)
     return s;
 }
 
-int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st)
+namespace {
+
+// Longest K first: workgroups are dispatched in job order, so the long row
+// blocks start early and the short ones fill in behind them.
+std::vector<size_t> longest_first(const std::vector<Req> &reqs)
+{
+    std::vector<size_t> order(reqs.size());
+    for (size_t i = 0; i < order.size(); ++i)
+        order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return reqs[a].K > reqs[b].K; });
+    return order;
+}
+
+}  // namespace
+
+std::vector<int> plan_splits(const std::vector<Req> &reqs)
+{
+    std::vector<int> out(reqs.size(), 1);
+    const std::vector<size_t> order = longest_first(reqs);
+    // the DMA jobs are one launch, the element-load jobs another
+    for (int v = 0; v < 2; ++v) {
+        std::vector<SplitShape> sh;
+        std::vector<size_t> at;
+        for (size_t oi : order)
+            if (reqs[oi].avec == (v == 1)) {
+                const Req &q = reqs[oi];
+                sh.push_back(SplitShape{static_cast<int>(cdiv(q.M, kBM)), q.K, q.part ? max_splits(q.M, q.K) : 1});
+                at.push_back(oi);
+            }
+        if (sh.empty())
+            continue;
+        const std::vector<int> sp = choose_splits(sh, reqs[at[0]].NP);
+        for (size_t i = 0; i < at.size(); ++i)
+            out[at[i]] = sp[i];
+    }
+    return out;
+}
+
+int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits_out)
 {
     if (reqs.empty())
         return ACSC_OK;
@@ -1164,32 +1288,22 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
             return set_error(ACSC_EINVAL, "pass: a tiled operand must be aligned and have ceil(columns / 64) tiles "
                                           "per tile row");
     }
-    // Split K only as far as needed for one workgroup per CU over the batch.
-    int64_t blocks = 0;
-    for (const auto &q : reqs)
-        blocks += cdiv(q.M, kBM);
-    int want = 1;
-    while (want < 16 && blocks * want < 256)
-        want *= 2;
-    // Longest K first: workgroups are dispatched in job order, so the long
-    // row blocks start early and the short ones fill in behind them.
-    std::vector<size_t> order(reqs.size());
-    for (size_t i = 0; i < order.size(); ++i)
-        order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return reqs[a].K > reqs[b].K; });
+    const std::vector<size_t> order = longest_first(reqs);
     std::vector<Job> sj;                 // element-load jobs
     std::vector<const Req *> vq;         // DMA jobs
     std::vector<int> vsplits, vchunk;
     std::vector<RedJob> red;
     int gx = 1;
     int64_t rtot = 1;
+    const std::vector<int> nsplit = plan_splits(reqs);
     for (size_t oi : order) {
         const Req &q = reqs[oi];
-        int splits = std::min(want, max_splits(q.M, q.K));
+        const int splits = nsplit[oi];
         const int64_t chunk = round_up(cdiv(q.K, splits), kBK);
-        splits = static_cast<int>(std::max<int64_t>(1, cdiv(q.K, chunk)));
         const int64_t ss = static_cast<int64_t>(q.M) * NP;
-        if (splits > 1) {
+        if (splits_out)
+            splits_out[oi] = splits;
+        if (splits > 1 && !splits_out) {
             red.push_back(RedJob{q.part, ss, q.C, q.ldc, q.M, NP, splits});
             rtot = std::max<int64_t>(rtot, static_cast<int64_t>(q.M) * (NP / 4));
         }

@@ -379,10 +379,16 @@ constexpr int kGWaves = 8;                         // waves per Gram workgroup
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct GramJob {
-    const float *A;
+    float *A;
     int64_t lda;
     int rows, rows_per_block, blocks;
     double *part;
+    // > 1: A is still in that many partials of a pass (row stride KP, stride
+    // rows * KP), which are added in order as they are read, and stored to A:
+    // each row is read by one workgroup only, so a launch that would only add
+    // them up (4 to 7 us) is saved
+    const float *src;
+    int splits;
 };
 
 // Staged row pitch in doubles: an odd multiple of 128 bytes, so that the two
@@ -425,10 +431,14 @@ __device__ __forceinline__ void gram_mfmas(v4d *acc, const double (&op)[NB], std
 
 // Wave W's share of the upper tiles: t = W, W + kGWaves, ...  (compile-time, so
 // that the operand registers are indexed by constants).
-template <int NB, int W>
+template <int NB, int W, bool PARTS>
 __device__ __forceinline__ void gram_wave(double *Ys0, double *Ys1, int lane, int nchunks,
-                                          const float *A, int64_t lda, int r0, int r1, int KP, double *pb, int tid)
+                                          const GramJob &J, int r0, int r1, int KP, double *pb, int tid)
 {
+    float *A = J.A;
+    const int64_t lda = J.lda;
+    const int splits = J.splits;
+    const int64_t ss = static_cast<int64_t>(J.rows) * KP;
     constexpr int NTILES = NB * (NB + 1) / 2;
     constexpr int TPW = NTILES > W ? (NTILES - W + kGWaves - 1) / kGWaves : 0;
     constexpr int NTH = 64 * kGWaves;              // threads
@@ -447,8 +457,14 @@ __device__ __forceinline__ void gram_wave(double *Ys0, double *Ys1, int lane, in
             const int rr = idx / q4, c4 = (idx % q4) * 4;
             const int gr = rb + rr;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (idx < kGRows * q4 && gr < r1 && c4 < KP)
-                v = *reinterpret_cast<const float4 *>(A + static_cast<int64_t>(gr) * lda + c4);
+            if (idx < kGRows * q4 && gr < r1 && c4 < KP) {
+                if constexpr (PARTS) {
+                    v = sum_partials(J.src + static_cast<int64_t>(gr) * KP + c4, ss, splits);
+                    *reinterpret_cast<float4 *>(A + static_cast<int64_t>(gr) * lda + c4) = v;
+                } else {
+                    v = *reinterpret_cast<const float4 *>(A + static_cast<int64_t>(gr) * lda + c4);
+                }
+            }
             pf[u] = v;
         }
     };
@@ -510,7 +526,7 @@ __device__ __forceinline__ void gram_wave(double *Ys0, double *Ys1, int lane, in
     }
 }
 
-template <int NB>
+template <int NB, bool PARTS>
 __global__ __launch_bounds__(64 * kGWaves) void gram_partial_kernel(const Batch<GramJob> jb, int KP)
 {
     const GramJob &J = jb.j[blockIdx.z];
@@ -525,14 +541,14 @@ __global__ __launch_bounds__(64 * kGWaves) void gram_partial_kernel(const Batch<
     const int nchunks = (r1 - r0 + kGRows - 1) / kGRows;
     double *pb = J.part + static_cast<int64_t>(blockIdx.x) * KP * KP;
     switch (wave) {
-    case 0: gram_wave<NB, 0>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 1: gram_wave<NB, 1>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 2: gram_wave<NB, 2>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 3: gram_wave<NB, 3>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 4: gram_wave<NB, 4>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 5: gram_wave<NB, 5>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    case 6: gram_wave<NB, 6>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
-    default: gram_wave<NB, 7>(Ys[0], Ys[1], lane, nchunks, J.A, J.lda, r0, r1, KP, pb, tid); break;
+    case 0: gram_wave<NB, 0, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 1: gram_wave<NB, 1, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 2: gram_wave<NB, 2, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 3: gram_wave<NB, 3, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 4: gram_wave<NB, 4, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 5: gram_wave<NB, 5, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    case 6: gram_wave<NB, 6, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
+    default: gram_wave<NB, 7, PARTS>(Ys[0], Ys[1], lane, nchunks, J, r0, r1, KP, pb, tid); break;
     }
 }
 
@@ -1807,9 +1823,37 @@ struct AdamCtx {
     float *norm_out;        // device or NULL
 };
 
+template <int NB>
+void gram_launch_nb(bool parts, const std::vector<GramJob> &gj, dim3 grid, int KP, hipStream_t st)
+{
+    if (parts)
+        launch_jobs("sc_gram", gram_partial_kernel<NB, true>, gj, grid, dim3(64 * kGWaves), 0, st, KP);
+    else
+        launch_jobs("sc_gram", gram_partial_kernel<NB, false>, gj, grid, dim3(64 * kGWaves), 0, st, KP);
+}
+
+void gram_launch(int nt, bool parts, const std::vector<GramJob> &gj, dim3 grid, int KP, hipStream_t st)
+{
+    switch (nt) {
+    case 1: gram_launch_nb<1>(parts, gj, grid, KP, st); break;
+    case 2: gram_launch_nb<2>(parts, gj, grid, KP, st); break;
+    case 3: gram_launch_nb<3>(parts, gj, grid, KP, st); break;
+    case 4: gram_launch_nb<4>(parts, gj, grid, KP, st); break;
+    case 5: gram_launch_nb<5>(parts, gj, grid, KP, st); break;
+    case 6: gram_launch_nb<6>(parts, gj, grid, KP, st); break;
+    case 7: gram_launch_nb<7>(parts, gj, grid, KP, st); break;
+    case 8: gram_launch_nb<8>(parts, gj, grid, KP, st); break;
+    case 9: gram_launch_nb<9>(parts, gj, grid, KP, st); break;
+    case 10: gram_launch_nb<10>(parts, gj, grid, KP, st); break;
+    case 11: gram_launch_nb<11>(parts, gj, grid, KP, st); break;
+    default: gram_launch_nb<12>(parts, gj, grid, KP, st); break;
+    }
+}
+
 // Gram matrices (fp64) of the first KP columns of one block per matrix.
-void gram(const std::vector<Mat> &ms, const std::vector<const float *> &A, const std::vector<int> &rows,
-          hipStream_t st)
+// `splits`: the partials (in pw.part) that each block still lies in, or 1.
+void gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::vector<int> &rows,
+          const std::vector<int> &splits, hipStream_t st)
 {
     const int KP = ms[0].D.KP;
     const int nt = static_cast<int>(cdiv(KP, kGT));
@@ -1836,24 +1880,17 @@ void gram(const std::vector<Mat> &ms, const std::vector<const float *> &A, const
     for (size_t i = 0; i < ms.size(); ++i) {
         const int rpb = static_cast<int>(rpb_of(i, rpb_batch));
         const int gb = static_cast<int>(cdiv(rows[i], rpb));
-        gj.push_back(GramJob{A[i], KP, rows[i], rpb, gb, ms[i].pw.gpart});
+        gj.push_back(GramJob{A[i], KP, rows[i], rpb, gb, ms[i].pw.gpart, ms[i].pw.part, splits[i]});
         rj.push_back(GramRedJob{ms[i].pw.gpart, gb, ms[i].pw.gram});
         gy = std::max(gy, gb);
     }
-    switch (nt) {
-    case 1: launch_jobs("sc_gram", gram_partial_kernel<1>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 2: launch_jobs("sc_gram", gram_partial_kernel<2>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 3: launch_jobs("sc_gram", gram_partial_kernel<3>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 4: launch_jobs("sc_gram", gram_partial_kernel<4>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 5: launch_jobs("sc_gram", gram_partial_kernel<5>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 6: launch_jobs("sc_gram", gram_partial_kernel<6>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 7: launch_jobs("sc_gram", gram_partial_kernel<7>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 8: launch_jobs("sc_gram", gram_partial_kernel<8>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 9: launch_jobs("sc_gram", gram_partial_kernel<9>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 10: launch_jobs("sc_gram", gram_partial_kernel<10>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    case 11: launch_jobs("sc_gram", gram_partial_kernel<11>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    default: launch_jobs("sc_gram", gram_partial_kernel<12>, gj, dim3(gy), dim3(64 * kGWaves), 0, st, KP); break;
-    }
+    bool parts = false;
+    for (int sp : splits)
+        parts = parts || sp > 1;
+    for (size_t i = 0; i < ms.size() && parts; ++i)
+        if (splits[i] <= 1)
+            gj[i].src = A[i];   // a whole product among cut ones: one "partial", added to nothing
+    gram_launch(nt, parts, gj, dim3(gy), KP, st);
     launch_jobs("sc_gram_reduce", gram_reduce_kernel, rj, dim3(static_cast<unsigned>(cdiv(int64_t(KP) * KP, 32))),
                 dim3(256), 0, st, KP);
 }
@@ -1865,17 +1902,19 @@ void gram(const std::vector<Mat> &ms, const std::vector<const float *> &A, const
 // 1e-7 * cond(Y); the iteration only needs a well-conditioned basis, and the
 // final basis gets the second pass.  The last pass also writes the bf16
 // transposed copy that the next streaming pass reads.
-int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, hipStream_t st)
+// `splits`: as for gram().
+int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::vector<int> splits, hipStream_t st)
 {
     const Dims &d0 = ms[0].D;
-    std::vector<const float *> A;
+    std::vector<float *> A;
     std::vector<int> rows;
     for (auto &m : ms) {
         A.push_back(onY ? m.pw.Y : m.pw.Z);
         rows.push_back(onY ? m.D.m : m.D.n);
     }
     for (int pass = 0; pass < passes; ++pass) {
-        gram(ms, A, rows, st);
+        gram(ms, A, rows, splits, st);
+        splits.assign(ms.size(), 1);   // added up by the Gram kernel
         std::vector<chol::Req> cj;
         for (auto &m : ms)
             cj.push_back(chol::Req{m.pw.gram, m.pw.T});
@@ -1885,7 +1924,7 @@ int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, hipSt
         // basis; otherwise (bf16 passes) only its bf16 transposed copy is
         std::vector<orth::Req> g;
         for (size_t i = 0; i < ms.size(); ++i) {
-            float *Y = const_cast<float *>(A[i]);
+            float *Y = A[i];
             uint16_t *t16 = (use16 && pass + 1 == passes) ? (onY ? ms[i].pw.Yt16 : ms[i].pw.Zt16) : nullptr;
             const int64_t ldt = onY ? ms[i].pw.ldy16 : ms[i].pw.ldz16;
             g.push_back(orth::Req{Y, rows[i], ms[i].pw.T, t16, ldt, !use16 || passes == 2});
@@ -1959,19 +1998,24 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
             launch_jobs("sc_init", init_block_kernel, j, dim3(grid1d(tot)), dim3(256), 0, st, k, KP, r);
         }
     }
-    // one pass Y = M Z  /  Z = M^T Y over every EMA (bf16 shadow on matrix cores, or fp32)
+    // one pass Y = M Z  /  Z = M^T Y over every EMA (bf16 shadow on matrix cores, or fp32);
+    // `splits` takes the partials that the bf16 products are left in
+    auto reqs16 = [&](bool mz) {
+        std::vector<pass::Req> q;
+        for (auto &m : ms) {
+            if (mz)
+                q.push_back(pass::Req{m.pw.M16, 0, true, m.pw.Zt16, m.pw.ldz16, m.pw.Y, KP, m.D.m, m.D.n,
+                                    KP, m.pw.part, static_cast<int>(m.pw.ntc16)});
+            else
+                q.push_back(pass::Req{m.pw.M16, 0, true, m.pw.Yt16, m.pw.ldy16, m.pw.Z, KP, m.D.n, m.D.m,
+                                    KP, m.pw.part, static_cast<int>(m.pw.ntc16)});
+        }
+        return q;
+    };
+    std::vector<int> splits(ms.size(), 1);
     auto pass = [&](bool mz) {
         if (use16) {
-            std::vector<pass::Req> q;
-            for (auto &m : ms) {
-                if (mz)
-                    q.push_back(pass::Req{m.pw.M16, 0, true, m.pw.Zt16, m.pw.ldz16, m.pw.Y, KP, m.D.m, m.D.n,
-                                        KP, m.pw.part, static_cast<int>(m.pw.ntc16)});
-                else
-                    q.push_back(pass::Req{m.pw.M16, 0, true, m.pw.Yt16, m.pw.ldy16, m.pw.Z, KP, m.D.n, m.D.m,
-                                        KP, m.pw.part, static_cast<int>(m.pw.ntc16)});
-            }
-            return mz ? pass::run("sc_pass_mz", false, q, st) : pass::run("sc_pass_mtq", true, q, st);
+            return pass::run(mz ? "sc_pass_mz" : "sc_pass_mtq", !mz, reqs16(mz), st, splits.data());
         } else {
             std::vector<GemmReq<float, float>> q;
             for (auto &m : ms) {
@@ -1994,16 +2038,16 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         rc = fused ? pass::ema_run("sc_ema", er, beta, omb, st) : pass(true);
         if (rc)
             return rc;
-        if ((rc = orthonormalise(ms, true, power_iters == 0 ? 2 : 1, use16, st)))
+        if ((rc = orthonormalise(ms, true, power_iters == 0 ? 2 : 1, use16, splits, st)))
             return rc;
         for (int it = 0; it < power_iters; ++it) {
             if ((rc = pass(false)))
                 return rc;
-            if ((rc = orthonormalise(ms, false, 1, use16, st)))
+            if ((rc = orthonormalise(ms, false, 1, use16, splits, st)))
                 return rc;
             if ((rc = pass(true)))
                 return rc;
-            if ((rc = orthonormalise(ms, true, it + 1 == power_iters ? 2 : 1, use16, st)))
+            if ((rc = orthonormalise(ms, true, it + 1 == power_iters ? 2 : 1, use16, splits, st)))
                 return rc;
         }
         // Z = M^T Q (= B^T) for the Rayleigh-Ritz step: B B^T = Z^T Z = L L^T, SVD of L by Jacobi.
@@ -2017,17 +2061,20 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
     if (!(phases & kPhaseRitz))
         return ACSC_OK;
     {
-        std::vector<const float *> A;
+        std::vector<float *> A;
         std::vector<int> rows;
         std::vector<chol::Req> cj;
         std::vector<JacJob> jj;
+        // the last product of the subspace phase lies in the partials of its plan
+        if (use16)
+            splits = pass::plan_splits(reqs16(false));
         for (auto &m : ms) {
             A.push_back(m.pw.Z);
             rows.push_back(m.D.n);
             cj.push_back(chol::Req{m.pw.gram, nullptr});
             jj.push_back(JacJob{m.pw.gram, m.pw.Bu, m.pw.Bv, m.in->s, m.in->d, m.pw.info});
         }
-        gram(ms, A, rows, st);
+        gram(ms, A, rows, splits, st);
         if ((rc = chol::run("sc_chol", cj, k, KP, false, st)))
             return rc;
         // the sweep cap can be lowered (not raised) through the environment, so
@@ -2276,6 +2323,8 @@ struct CropJob {
     int64_t lds;
     float *dst;
     int rows, cols;
+    int splits;      // > 1: src is the first of that many partials, ss apart, added in order
+    int64_t ss;
 };
 
 __global__ __launch_bounds__(256) void crop_kernel(const Batch<CropJob> jb)
@@ -2286,7 +2335,11 @@ __global__ __launch_bounds__(256) void crop_kernel(const Batch<CropJob> jb)
          idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const int64_t i = idx / J.cols;
         const int c = static_cast<int>(idx - i * J.cols);
-        J.dst[idx] = J.src[i * J.lds + c];
+        float v = J.src[i * J.lds + c];
+#pragma unroll 4
+        for (int p = 1; p < J.splits; ++p)
+            v += J.src[p * J.ss + i * J.lds + c];
+        J.dst[idx] = v;
     }
 }
 
@@ -2333,9 +2386,18 @@ void crop(const char *tag, const std::vector<CropJob> &jobs, hipStream_t st)
     launch_jobs(tag, crop_kernel, jobs, dim3(grid1d(tot)), dim3(256), 0, st);
 }
 
+// The first r columns of a product [rows, KP] into the caller's factor; a bf16
+// pass cut along k is still in the workspace's partials.
+CropJob crop_of(const PsgdItem &x, const float *src, int rows, float *dst, int r, int splits)
+{
+    const int KP = x.mat.D.KP;
+    return CropJob{splits > 1 ? x.w.pw.part : src, KP, dst, rows, r, splits, static_cast<int64_t>(rows) * KP};
+}
+
 int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t st)
 {
     const int KP = it[0].mat.D.KP;
+    std::vector<int> splits(it.size(), 1);
     if (use16) {
         // Q^T in bf16, rows r .. KP-1 zero: the thin factor of the pass
         std::vector<TileJob> tj;
@@ -2362,7 +2424,7 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
             }
             launch_jobs("psgd_feedback", ema_shadow_kernel<uint16_t>, j, dim3(grid1d(tot)), dim3(256), 0, st, 1.0f,
                         1.0f);
-            if (int rc = pass::run("psgd_pass_mq", false, q, st))
+            if (int rc = pass::run("psgd_pass_mq", false, q, st, splits.data()))
                 return rc;
         }
     } else {
@@ -2384,8 +2446,8 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
         tall_gemm<float, false, float>("psgd_pass_mq", q, st);
     }
     std::vector<CropJob> cj;
-    for (auto &x : it)
-        cj.push_back(CropJob{x.w.pw.Y, KP, x.in->P, x.in->m, r});
+    for (size_t i = 0; i < it.size(); ++i)
+        cj.push_back(crop_of(it[i], it[i].w.pw.Y, it[i].in->m, it[i].in->P, r, splits[i]));
     crop("psgd_crop", cj, st);
     return ACSC_OK;
 }
@@ -2406,18 +2468,19 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
     for (auto &x : it)
         ms.push_back(x.mat);
     // CholeskyQR2: Y <- P_hat (fp32), and its bf16 transposed copy for the pass
-    if (int rc = orthonormalise(ms, true, 2, use16, st))
+    if (int rc = orthonormalise(ms, true, 2, use16, std::vector<int>(ms.size(), 1), st))
         return rc;
     std::vector<CropJob> cj;
     for (auto &x : it)
-        cj.push_back(CropJob{x.w.pw.Y, KP, x.in->P, x.in->m, r});
+        cj.push_back(crop_of(x, x.w.pw.Y, x.in->m, x.in->P, r, 1));
     crop("psgd_crop", cj, st);
+    std::vector<int> splits(it.size(), 1);
     if (use16) {
         std::vector<pass::Req> q;
         for (auto &x : it)
             q.push_back(pass::Req{x.w.pw.M16, 0, true, x.w.pw.Yt16, x.w.pw.ldy16, x.w.pw.Z, KP, x.in->n,
                                   x.in->m, KP, x.w.pw.part, static_cast<int>(x.w.pw.ntc16)});
-        if (int rc = pass::run("psgd_pass_mtp", true, q, st))
+        if (int rc = pass::run("psgd_pass_mtp", true, q, st, splits.data()))
             return rc;
     } else {
         std::vector<GemmReq<float, float>> q;
@@ -2427,8 +2490,8 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
         tall_gemm<float, true, float>("psgd_pass_mtp", q, st);
     }
     cj.clear();
-    for (auto &x : it)
-        cj.push_back(CropJob{x.w.pw.Z, KP, x.in->Q, x.in->n, r});
+    for (size_t i = 0; i < it.size(); ++i)
+        cj.push_back(crop_of(it[i], it[i].w.pw.Z, it[i].in->n, it[i].in->Q, r, splits[i]));
     crop("psgd_crop", cj, st);
     return ACSC_OK;
 }

@@ -44,8 +44,15 @@ inline int64_t tiled_elems(int64_t R, int64_t C) { return tiles_per_row(R) * til
 // caller sizes `part` for it.
 int max_splits(int64_t M, int64_t K);
 
-// Enqueue one pass per request (all requests share NP) on `st`.
-int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st);
+// The k pieces that run() cuts each request into (a function of the shapes).
+std::vector<int> plan_splits(const std::vector<Req> &reqs);
+
+// Enqueue one pass per request (all requests share NP) on `st`.  With
+// `splits` (one entry per request) a product that was cut along k is left as
+// that many partials (partial p at part + p * M * NP, row stride NP) for the
+// next kernel to add in order as it reads them, and C is not written; 1 means
+// that C holds the product.  Without it C always does.
+int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits = nullptr);
 
 // The anchor EMA fused with the first pass of the subspace iteration
 // (Sec. 3.2): M <- a M + b G (the EMA: a = beta, b = 1 - beta; error

@@ -97,6 +97,42 @@ def test_correct_stores_widths_that_are_no_multiple_of_8(pk, m, n, r):
     assert osp.rel_fro(_np(out), ref) <= TOL[torch.bfloat16]
 
 
+@pytest.mark.parametrize("shapes,r", [(((300, 5000), (256, 2100)), 16), (((2048, 1536), (257, 9000), (511, 4096)), 72),
+                                      (((1300, 3333), (200, 1024)), 40)])
+def test_passes_cut_into_uneven_pieces(pk, shapes, r):
+    """Small batches cut the long rows of a pass into pieces of a common
+    length (last pieces shorter, any piece count), whose partials the Gram
+    kernel or a reduction adds: a build and a correction against plain
+    PyTorch in 64 bits from the same bf16 inputs."""
+    spec = workloads.GradSpec(shapes, 24, (1.0, 10.0), (r,), torch.bfloat16, None, None)
+    items, pairs = [], [workloads.grad_pair(spec, 21, 0, i, "cpu") for i in range(len(shapes))]
+    for i, (m, n) in enumerate(shapes):
+        U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=m + n)
+        items.append(dict(G=pairs[i].G_mask.cuda(), prior=(U.float().cuda(), (s / (s + 0.7)).float().cuda(),
+                                                           V.float().cuda()),
+                          out=torch.empty(m, n, dtype=torch.bfloat16, device="cuda"),
+                          ws=pk.workspace(m, n, r, 0, torch.bfloat16)))
+    pk.sc_correct_batched(items, r, workloads.ALPHA)
+    torch.cuda.synchronize()
+    for it in items:
+        U, d, V = (_np(t) for t in it["prior"])
+        assert osp.rel_fro(_np(it["out"]), osp.correct(_np(it["G"]), U, d, V, workloads.ALPHA)) <= TOL[torch.bfloat16]
+    builds = []
+    for i, (m, n) in enumerate(shapes):
+        outs = (torch.empty(m, 24, device="cuda"), torch.empty(24, device="cuda"), torch.empty(n, 24, device="cuda"),
+                torch.empty(24, device="cuda"))
+        builds.append(dict(G_anc=pairs[i].G_anc.cuda(), M=torch.zeros(m, n, device="cuda"), out=outs,
+                           ws=pk.workspace(m, n, 24, 16, torch.bfloat16)))
+    pk.sc_build_prior_batched(builds, 24, workloads.BETA, workloads.TAU, 16, 3, seed=5)
+    torch.cuda.synchronize()
+    for it, gp in zip(builds, pairs):
+        M = (1 - workloads.BETA) * _np(gp.G_anc)
+        U0, s0, V0 = osp.top_r_svd_gram(M, 24)
+        U, s, V, d = it["out"]
+        assert np.max(np.abs(_np(s) - s0) / s0) < 5e-3
+        assert osp.projector_distance(_np(U), U0) < 2e-2 and osp.projector_distance(_np(V), V0) < 2e-2
+
+
 def test_correct_in_place_and_alpha_one(pk):
     m, n, r = 512, 384, 16
     U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=1)
