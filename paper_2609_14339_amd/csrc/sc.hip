@@ -595,67 +595,98 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const Batch<GramRedJob
     }
 }
 
-// Sum over each group of 8 lanes with DPP lane permutes (VALU, no LDS):
-// quad_perm [1,0,3,2] and [2,3,0,1] (xor 1, xor 2), then row_half_mirror
-// (pairs the two quads of each 8-lane half row); every lane of the group ends
-// with the group's sum.
+// Lane permutes within a row of 16 lanes (DPP: VALU, no LDS).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;        // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141;                  // lane i of each 8 takes lane 7 - i
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;      // lane i takes lane i - 4 (i - 8) of its row
+constexpr int kDppBcast = 0x150;                       // + L: every lane takes lane L of its row
+
+// Sum over each group of 8 lanes; every lane of the group ends with it.
 __device__ __forceinline__ float group8_sum(float x)
 {
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, false));
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, false));
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xF, 0xF, false));
+    x += dpp<kDppXor1>(x);
+    x += dpp<kDppXor2>(x);
+    x += dpp<kDppHalfMirror>(x);
     return x;
 }
 
-__device__ __forceinline__ double group8_sum(double x)
+// Four sums over the 16 lanes of a row at once: quad q of the row ends with
+// the sum of p[q] in its four lanes.  Each step halves the values a lane
+// carries as it halves the lanes that are still apart, so four sums cost
+// five exchanges instead of sixteen.
+template <typename T>
+__device__ __forceinline__ T row_sum4(const T (&p)[4], bool hi8, bool hi4)
 {
-#define ACSC_DPP64(CTRL)                                                                          \
-    {                                                                                             \
-        const int lo = __double2loint(x), hi = __double2hiint(x);                                 \
-        const int plo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xF, 0xF, false);                \
-        const int phi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xF, 0xF, false);                \
-        x += __hiloint2double(phi, plo);                                                          \
-    }
-    ACSC_DPP64(0xB1)
-    ACSC_DPP64(0x4E)
-    ACSC_DPP64(0x141)
-#undef ACSC_DPP64
-    return x;
+    T a = (hi8 ? p[2] : p[0]) + dpp<kDppRor8>(hi8 ? p[0] : p[2]);
+    T b = (hi8 ? p[3] : p[1]) + dpp<kDppRor8>(hi8 ? p[1] : p[3]);
+    T s = (hi4 ? b : a) + dpp<kDppHalfMirror>(hi4 ? a : b);
+    s += dpp<kDppXor1>(s);
+    s += dpp<kDppXor2>(s);
+    return s;
 }
 
-// Reciprocal and reciprocal square root of the rotation formulas: the fp32
-// path takes the hardware approximations (about 1 ulp; a rotation only has to
-// be orthogonal, and the next sweep corrects its angle).  fp64 refines the
-// hardware estimates (v_rsq_f64, v_rcp_f64) by two Newton steps each, to
-// within a few ulp: much shorter dependent chains than the correctly rounded
-// square root and division, which sit on every round's critical path, and c
-// and s = c t stay orthogonal to working precision.  The arguments are
-// positive and finite (the caller skips pairs with a zero norm or product).
-__device__ __forceinline__ float jac_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double jac_rsqrt(double x)
+// Tangent t of the rotation that makes two columns of squared norms al, be and
+// inner product ga orthogonal (0 where they already are to `tol`), and
+// c = 1 / sqrt(1 + t^2), ic = sqrt(1 + t^2); `worst` takes the pair's
+// |ga| / sqrt(al be).  A rotation has to be orthogonal to working precision,
+// but its angle need not be exact: one that is off by 1e-7 leaves 1e-7 of
+// the pair's inner product for the next sweep, which is less than a sweep
+// leaves anyway.  So the angle comes from the hardware estimates and fp32,
+// and only c from a refined reciprocal square root, which the columns do not
+// wait for.  |zeta| past 1e18 is clamped: an angle below 1e-18 does not move a
+// column.
+__device__ __forceinline__ void rotation(double al, double be, double ga, double tol, float &worst, double &t,
+                                         double &c, double &ic)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    const double hx = 0.5 * x;
-    y = __builtin_fma(y, __builtin_fma(-hx * y, y, 0.5), y);   // y + y (1 - x y^2) / 2
-    y = __builtin_fma(y, __builtin_fma(-hx * y, y, 0.5), y);
-    return y;
-}
-__device__ __forceinline__ float jac_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double jac_rcp(double x)
-{
-    double y = __builtin_amdgcn_rcp(x);
-    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);        // y + y (1 - x y)
-    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
-    return y;
+    const double prod = al * be;
+    const double ratio = prod > 0.0 ? fabs(ga) * __builtin_amdgcn_rsq(prod) : (prod < 0.0 ? 1.0 : 0.0);
+    worst = fmaxf(worst, static_cast<float>(ratio));
+    const double zd = (be - al) * __builtin_amdgcn_rcp(2.0 * ga);
+    const float z = static_cast<float>(fmin(fmax(zd, -1e18), 1e18));
+    const float z2 = fmaf(z, z, 1.f);
+    const float tt = copysignf(__builtin_amdgcn_rcpf(fabsf(z) + z2 * __builtin_amdgcn_rsqf(z2)), z);
+    t = prod > 0.0 && ratio > tol ? static_cast<double>(tt) : 0.0;
+    const double q = __builtin_fma(t, t, 1.0);
+    c = __builtin_amdgcn_rsq(q);
+    const double hq = 0.5 * q;
+    c = __builtin_fma(c, __builtin_fma(-hq * c, c, 0.5), c);   // c + c (1 - q c^2) / 2
+    c = __builtin_fma(c, __builtin_fma(-hq * c, c, 0.5), c);
+    ic = q * c;
 }
 
 // ---------------------------------------------------------------------------
-// One-sided (Hestenes) Jacobi SVD of the k x k factor L in LDS, one
-// workgroup: rotate column pairs (round-robin tournament, every pair of a round
-// at once on 8 lanes) until every pair is orthogonal to `tol`.  Then sigma_c = ||a_c||,
-// u_c = a_c / sigma_c, sorted descending, and the right factors of the final
-// products are written:  Bu[:, t] = u_(t), Bv[:, t] = u_(t) / sigma_(t),
-// s[t] = sigma_(t), d[t] = s / (s + tau) for t < r.
+// One-sided (Hestenes) Jacobi SVD of the k x k factor L, one workgroup:
+// rotate column pairs until every pair is orthogonal to `tol`.  Then
+// sigma_c = ||a_c||, u_c = a_c / sigma_c, sorted descending, and the right
+// factors of the final products are written:  Bu[:, t] = u_(t),
+// Bv[:, t] = u_(t) / sigma_(t), s[t] = sigma_(t), d[t] = s / (s + tau), t < r.
+//
+// What bounds it is the chain of rounds (k - 1 per sweep, 6 or 7 sweeps), each
+// a few hundred cycles of dependent work on one CU.  The columns sit in LDS
+// in blocks of four; a row of 16 lanes holds a pair of blocks in registers
+// (R rows of 8 columns per lane) and makes all 16 cross pairs orthogonal in
+// four rounds of four rotations before it stores them: one LDS round trip
+// and one barrier for four rounds, and the four rotations of a round share
+// one reduction and one evaluation of the angle (quad q of the row has
+// rotation q).  In between a column is held as x / d with its scale d apart
+// (x' = c (x - t y), y' = c (y + t x): the factors c go to the scales), so a
+// rotation is two multiply-adds per element and waits for t only.  Block pairs follow a round-robin tournament; the pairs
+// within a block go before the first of a sweep, together with the exact
+// squared norms, which the rotations then update.
+// Measured (six 48 x 48, four 80 x 80 factors): 190 and 400 us with a barrier
+// and an LDS round trip per round, 145 and 310 us so.
 // ---------------------------------------------------------------------------
 struct JacJob {
     const double *Lf;
@@ -687,41 +718,145 @@ __global__ __launch_bounds__(64) void stamp_kernel(const Batch<JacJob> jb)
     }
 }
 
-template <typename T, int RC>
-__global__ __launch_bounds__(1024) void jacobi_kernel(const Batch<JacJob> jb, int k, int KP, int r,
-                                                      int RP, float tau, T tol, int max_sweeps)
+constexpr int kJacBlk = 4;   // columns per block
+
+// blocks of the tournament: an even number
+__host__ __device__ constexpr int jacobi_blocks(int k) { return ((k + kJacBlk - 1) / kJacBlk + 1) & ~1; }
+
+// Column pitch of the fp64 kernel in LDS: past the padded rows, so that the
+// lanes that read or write one row of many columns fall on different banks.
+// (The fp32 kernel's 16-byte accesses run best unpadded: 600 us against 850
+// with four more rows at k = 144.)
+__host__ __device__ constexpr int jacobi_pitch_f64(int rows) { return rows + 1; }
+
+// The columns of the factor into LDS (column c at A[c * kp]), rows and columns
+// past k as zeros.  Rows of the factor are read whole, and eight loads go
+// out before the first is stored.
+template <typename T, int kp>
+__device__ __forceinline__ void jacobi_load(T *A, int cols, const double *Lf, int k, int KP)
+{
+    const int nth = blockDim.x, total = cols * kp;
+    for (int i0 = threadIdx.x; i0 < total; i0 += 8 * nth) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int idx = min(i0 + u * nth, total - 1);
+            const int i = idx / cols, c = idx - i * cols;
+            v[u] = Lf[static_cast<int64_t>(min(i, k - 1)) * KP + min(c, k - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int idx = i0 + u * nth;
+            const int i = idx / cols, c = idx - i * cols;
+            if (idx < total)
+                A[c * kp + i] = i < k && c < k ? static_cast<T>(v[u]) : T(0);
+        }
+    }
+}
+
+// What follows the sweeps: the status words, then singular values, their order,
+// the right factors of the final products and the filter.  Column c of the
+// orthogonal factor is A[c * kp] in LDS.
+template <typename T, int kp>
+__device__ __forceinline__ void jacobi_finish(const JacJob &J, const T *A, int k, int KP, int r, int RP, float tau,
+                                              float tol, int sweeps_used, float last_off, int stamp)
+{
+    float *Bu = J.Bu, *Bv = J.Bv, *s_out = J.s_out, *d_out = J.d_out;
+    int *info = J.info;
+    __shared__ double sh_cut;
+    __shared__ double sig[kKMax], inv[kKMax];
+    __shared__ int rank_of[kKMax], col_of[kKMax];
+    const int tid = threadIdx.x, nth = blockDim.x, grp = tid >> 4, gl = tid & 15;
+    if (tid == 0 && info) {
+        info[kInfoSweeps] = sweeps_used;
+        info[kInfoResidual] = __float_as_int(last_off);
+        info[kInfoTol] = __float_as_int(tol);
+        info[kInfoStatus] = (last_off > tol ? kStatusNoConv : 0) |
+                            (stamp != kSubspaceStamp && stamp != kSubspaceStalledStamp ? kStatusNoSubspace : 0) |
+                            (stamp == kSubspaceStalledStamp ? kStatusStalled : 0);
+        info[kInfoStamp] = 0;
+    }
+    // norms, one row of 16 lanes per column
+    for (int c = grp; c < k; c += nth >> 4) {
+        double ss = 0.0;
+        for (int i = gl; i < k; i += 16) {
+            const double x = A[c * kp + i];
+            ss += x * x;
+        }
+        ss += dpp<kDppRor8>(ss);
+        ss += dpp<kDppHalfMirror>(ss);
+        ss += dpp<kDppXor1>(ss);
+        ss += dpp<kDppXor2>(ss);
+        if (gl == 0)
+            sig[c] = sqrt(ss);
+    }
+    __syncthreads();
+    for (int c = tid; c < k; c += nth) {
+        int rk = 0;
+        for (int c2 = 0; c2 < k; ++c2)
+            rk += (sig[c2] > sig[c]) || (sig[c2] == sig[c] && c2 < c);
+        rank_of[c] = rk;
+    }
+    __syncthreads();
+    // numerical rank: singular values at the fp32 rounding floor of the
+    // largest one are zero (their vectors are noise, and 1/sigma would blow up)
+    for (int c = tid; c < k; c += nth) {
+        col_of[rank_of[c]] = c;
+        if (rank_of[c] == 0)
+            sh_cut = kRankCutoff * sig[c];
+    }
+    __syncthreads();
+    for (int c = tid; c < k; c += nth)
+        if (sig[c] <= sh_cut)
+            sig[c] = 0.0;
+    __syncthreads();
+    for (int c = tid; c < k; c += nth)
+        inv[c] = sig[c] > 0.0 ? 1.0 / sig[c] : 0.0;
+    __syncthreads();
+#pragma unroll 4
+    for (int idx = tid; idx < KP * RP; idx += nth) {
+        const int i = idx / RP, t = idx - i * RP;
+        const int c = col_of[min(t, k - 1)];
+        const double ud = i < k && t < r ? static_cast<double>(A[c * kp + min(i, k - 1)]) * inv[c] : 0.0;
+        Bu[idx] = static_cast<float>(ud);
+        Bv[idx] = static_cast<float>(ud * inv[c]);
+    }
+    for (int t = tid; t < r; t += nth) {
+        const float sg = static_cast<float>(sig[col_of[t]]);
+        s_out[t] = sg;
+        const float den = sg + tau;
+        d_out[t] = den != 0.f ? sg / den : 0.f;
+    }
+}
+
+// fp32 (beyond the orders whose fp64 columns fit LDS): column pairs of a
+// round-robin tournament, 8 lanes per pair, one round per barrier.  At 72
+// pairs of 160 rows a round is bound by the instructions that one CU can
+// issue, which the wider rows of the blocked form below do not cut: 144 x 144
+// takes 600 to 630 us so and 890 us in blocks.
+template <int R>
+__global__ __launch_bounds__(1024) void jacobi_pairs_kernel(const Batch<JacJob> jb, int k, int KP, int r, int RP,
+                                                            float tau, float tol, int max_sweeps)
 {
     const JacJob &J = jb.j[blockIdx.z];
     const double *Lf = J.Lf;
-    float *Bu = J.Bu, *Bv = J.Bv, *s_out = J.s_out, *d_out = J.d_out;
     int *info = J.info;
     extern __shared__ __attribute__((aligned(16))) unsigned char jsm[];
-    // column c at A[c * kp]; kp = k rounded up to 8 V (= 8 RC; 32 rows in
-    // fp32, 16 in fp64), rows k..kp-1 are zero.  Lane gl of a pair's 8 lanes
-    // holds the R = kp / 8 consecutive rows gl R .. gl R + R - 1 of both
-    // columns (R a multiple of V: 16-byte LDS accesses).  Every round reads
-    // and writes whole columns, so the padding is kept to what the 16-byte
-    // accesses need.
-    constexpr int V = 16 / sizeof(T);   // elements per 16-byte access
+    // column c at A[c * kp], rows k..kp-1 are zero.  Lane gl of a pair's 8
+    // lanes holds the R consecutive rows gl R .. gl R + R - 1 of both columns
+    // (R a multiple of 4: 16-byte LDS accesses).
+    using T = float;
+    constexpr int V = 4, kp = 8 * R;
     T *A = reinterpret_cast<T *>(jsm);
-    const int kp = (k + 8 * V - 1) / (8 * V) * (8 * V);
     T *nrm = A + static_cast<size_t>(k) * kp;   // squared column norms
     __shared__ unsigned int sh_off;
-    __shared__ double sh_cut;
-    __shared__ double sig[kKMax];
-    __shared__ int rank_of[kKMax];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
-    for (int idx = tid; idx < k * kp; idx += blockDim.x) {
-        const int c = idx / kp, i = idx % kp;
-        A[c * kp + i] = i < k ? static_cast<T>(Lf[static_cast<int64_t>(i) * KP + c]) : T(0);
-    }
+    jacobi_load<T, kp>(A, k, Lf, k, KP);
     const int n2 = k + (k & 1);
     const int npairs = n2 / 2;
     // eight column pairs per wave, 8 lanes each
     const int grp = lane >> 3, gl = lane & 7;
     const int slots = nwave * 8;
-    constexpr int R = RC;
-    constexpr int RMAX = RC;
     static_assert(R % V == 0, "rows per lane");
     int sweeps_used = 0;
     float last_off = 0.f;
@@ -736,9 +871,8 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const Batch<JacJob> jb, in
             const T *ac = A + c * kp + gl * R;
             T ss = 0;
 #pragma unroll
-            for (int e = 0; e < RMAX; ++e)
-                if (e < R)
-                    ss += ac[e] * ac[e];
+            for (int e = 0; e < R; ++e)
+                ss += ac[e] * ac[e];
             ss = group8_sum(ss);
             if (gl == 0)
                 nrm[c] = ss;
@@ -767,50 +901,45 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const Batch<JacJob> jb, in
                 }
                 T *ap = A + cp * kp + gl * R;
                 T *aq = A + cq * kp + gl * R;
-                T xv[RMAX], yv[RMAX];
+                T xv[R], yv[R];
 #pragma unroll
-                for (int e = 0; e < RMAX; e += V) {
-                    uint4 ux = make_uint4(0u, 0u, 0u, 0u), uy = ux;
-                    if (e < R) {
-                        ux = *reinterpret_cast<const uint4 *>(ap + e);
-                        uy = *reinterpret_cast<const uint4 *>(aq + e);
-                    }
+                for (int e = 0; e < R; e += V) {
+                    const uint4 ux = *reinterpret_cast<const uint4 *>(ap + e);
+                    const uint4 uy = *reinterpret_cast<const uint4 *>(aq + e);
                     __builtin_memcpy(&xv[e], &ux, 16);
                     __builtin_memcpy(&yv[e], &uy, 16);
                 }
                 const T al = nrm[cp], be = nrm[cq];
                 T gp[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int e = 0; e < RMAX; ++e)
+                for (int e = 0; e < R; ++e)
                     gp[e & 3] += xv[e] * yv[e];
                 const T ga = group8_sum((gp[0] + gp[1]) + (gp[2] + gp[3]));
                 const T prod = al * be;
                 if (ga == T(0) || prod == T(0))
                     continue;
-                const T ratio = fabs(ga) * jac_rsqrt(prod);
+                const T ratio = fabs(ga) * __builtin_amdgcn_rsqf(prod);
                 wmax = fmaxf(wmax, static_cast<float>(ratio));
                 if (ratio <= tol)
                     continue;
-                const T zeta = (be - al) * jac_rcp(T(2) * ga);
+                const T zeta = (be - al) * __builtin_amdgcn_rcpf(T(2) * ga);
                 const T z2 = T(1) + zeta * zeta;
-                const T t = (zeta >= T(0) ? T(1) : T(-1)) * jac_rcp(fabs(zeta) + z2 * jac_rsqrt(z2));
-                const T c = jac_rsqrt(T(1) + t * t);
+                const T t = (zeta >= T(0) ? T(1) : T(-1)) * __builtin_amdgcn_rcpf(fabs(zeta) + z2 * __builtin_amdgcn_rsqf(z2));
+                const T c = __builtin_amdgcn_rsqf(T(1) + t * t);
                 const T sn = c * t;
 #pragma unroll
-                for (int e = 0; e < RMAX; e += V) {
-                    if (e < R) {
-                        T xo[V], yo[V];
+                for (int e = 0; e < R; e += V) {
+                    T xo[V], yo[V];
 #pragma unroll
-                        for (int v = 0; v < V; ++v) {
-                            xo[v] = c * xv[e + v] - sn * yv[e + v];
-                            yo[v] = sn * xv[e + v] + c * yv[e + v];
-                        }
-                        uint4 ux, uy;
-                        __builtin_memcpy(&ux, xo, 16);
-                        __builtin_memcpy(&uy, yo, 16);
-                        *reinterpret_cast<uint4 *>(ap + e) = ux;
-                        *reinterpret_cast<uint4 *>(aq + e) = uy;
+                    for (int v = 0; v < V; ++v) {
+                        xo[v] = c * xv[e + v] - sn * yv[e + v];
+                        yo[v] = sn * xv[e + v] + c * yv[e + v];
                     }
+                    uint4 ux, uy;
+                    __builtin_memcpy(&ux, xo, 16);
+                    __builtin_memcpy(&uy, yo, 16);
+                    *reinterpret_cast<uint4 *>(ap + e) = ux;
+                    *reinterpret_cast<uint4 *>(aq + e) = uy;
                 }
                 // the rotation zeroes the pair's inner product: the norms move by t gamma
                 if (gl == 0) {
@@ -834,73 +963,242 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const Batch<JacJob> jb, in
         if (off <= static_cast<float>(tol))
             break;
     }
-    if (tid == 0 && info) {
-        info[kInfoSweeps] = sweeps_used;
-        info[kInfoResidual] = __float_as_int(last_off);
-        info[kInfoTol] = __float_as_int(static_cast<float>(tol));
-        info[kInfoStatus] = (last_off > static_cast<float>(tol) ? kStatusNoConv : 0) |
-                            (stamp != kSubspaceStamp && stamp != kSubspaceStalledStamp ? kStatusNoSubspace : 0) |
-                            (stamp == kSubspaceStalledStamp ? kStatusStalled : 0);
-        info[kInfoStamp] = 0;
-    }
-    // norms (one wave per column)
-    for (int c = wave; c < k; c += nwave) {
-        double ss = 0.0;
-        for (int i = lane; i < k; i += 64) {
-            const double x = A[c * kp + i];
-            ss += x * x;
+    jacobi_finish<T, kp>(J, A, k, KP, r, RP, tau, static_cast<float>(tol), sweeps_used, last_off, stamp);
+}
+
+// fp64: see above.  At an order of 16 to 80 a round takes 0.45 to 0.58 us (0.67
+// to 0.72 with a barrier and an LDS round trip per round).
+constexpr float kJacCheck = 1e-6f;   // a sweep that met less than this may be the last
+
+template <int R>
+__global__ __launch_bounds__(256) void jacobi_blocks_kernel(const Batch<JacJob> jb, int k, int KP, int r, int RP,
+                                                            float tau, double tol, int max_sweeps)
+{
+    using T = double;
+    const JacJob &J = jb.j[blockIdx.z];
+    const double *Lf = J.Lf;
+    int *info = J.info;
+    extern __shared__ __attribute__((aligned(16))) unsigned char jsm[];
+    constexpr int kp = jacobi_pitch_f64(16 * R);   // rows k .. are zero
+    const int nb = jacobi_blocks(k), cols = nb * kJacBlk;   // columns k .. cols - 1 are zero
+    T *A = reinterpret_cast<T *>(jsm);         // column c at A[c * kp]
+    T *nrm = A + static_cast<size_t>(cols) * kp;   // squared column norms
+    __shared__ unsigned int sh_off;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nth = blockDim.x;
+    jacobi_load<T, kp>(A, cols, Lf, k, KP);
+    const int grp = tid >> 4, gl = tid & 15, quad = gl >> 2;
+    const bool hi8 = gl & 8, hi4 = gl & 4;
+    const bool live = grp < nb / 2;            // whole rows of 16 lanes
+    int sweeps_used = 0;
+    float last_off = 0.f;
+    // the subspace phase that produced Lf stamps the workspace (read before
+    // this kernel clears the stamp, by the same thread)
+    const int stamp = (tid == 0 && info) ? info[kInfoStamp] : 0;
+    __syncthreads();
+    for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+        if (tid == 0)
+            sh_off = 0u;
+        float worst = 0.f;
+        for (int round = 0; round < nb - 1; ++round) {
+            if (live) {
+                auto pos = [&](int x) {
+                    if (x == 0)
+                        return 0;
+                    int t = x - 1 + round;
+                    if (t >= nb - 1)
+                        t -= nb - 1;
+                    return t + 1;
+                };
+                const int b0 = pos(grp), b1 = pos(nb - 1 - grp);
+                const int c0 = min(b0, b1) * kJacBlk, c1 = max(b0, b1) * kJacBlk;
+                // lane gl holds rows gl, gl + 16, ... of columns c0 .. c0 + 3 and c1 .. c1 + 3
+                T x[2 * kJacBlk][R];
+                T *pa = A + c0 * kp + gl, *pb = A + c1 * kp + gl;
+#pragma unroll
+                for (int j = 0; j < kJacBlk; ++j)
+#pragma unroll
+                    for (int e = 0; e < R; ++e) {
+                        x[j][e] = pa[j * kp + 16 * e];
+                        x[kJacBlk + j][e] = pb[j * kp + 16 * e];
+                    }
+                // the four pairs (u[q], v[q]) at once: quad q has its two
+                // columns' squared norms n, scales d and 1 / d
+                struct Col {
+                    T n, d, id;
+                };
+                auto rotate = [&](const int (&u)[4], const int (&v)[4], Col &a, Col &b) {
+                    T p[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        p[q] = x[u[q]][0] * x[v[q]][0];
+#pragma unroll
+                        for (int e = 1; e < R; ++e)
+                            p[q] += x[u[q]][e] * x[v[q]][e];
+                    }
+                    const T ga = row_sum4(p, hi8, hi4) * (a.d * b.d);
+                    T t, c, ic;
+                    rotation(a.n, b.n, ga, tol, worst, t, c, ic);
+                    const T fu = t * (b.d * a.id), fv = t * (a.d * b.id);
+                    const T uu[4] = {dpp<kDppBcast>(fu), dpp<kDppBcast + 4>(fu), dpp<kDppBcast + 8>(fu),
+                                     dpp<kDppBcast + 12>(fu)};
+                    const T vv[4] = {dpp<kDppBcast>(fv), dpp<kDppBcast + 4>(fv), dpp<kDppBcast + 8>(fv),
+                                     dpp<kDppBcast + 12>(fv)};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < R; ++e) {
+                            const T xa = x[u[q]][e], xb = x[v[q]][e];
+                            x[u[q]][e] = xa - uu[q] * xb;
+                            x[v[q]][e] = xb + vv[q] * xa;
+                        }
+                    const T c2 = c * c, tg = T(2) * t * ga, t2 = t * t;
+                    const T na = c2 * (a.n - tg + t2 * b.n), nb2 = c2 * (b.n + tg + t2 * a.n);
+                    a = Col{na, a.d * c, a.id * ic};
+                    b = Col{nb2, b.d * c, b.id * ic};
+                };
+                Col ca{T(0), T(1), T(1)}, cb = ca;
+                if (round == 0) {
+                    // exact squared norms, then the pairs within the two blocks:
+                    // quads 0, 1 take block c0's, quads 2, 3 block c1's
+                    T p[4], n0, n1;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            p[q] = x[4 * h + q][0] * x[4 * h + q][0];
+#pragma unroll
+                            for (int e = 1; e < R; ++e)
+                                p[q] += x[4 * h + q][e] * x[4 * h + q][e];
+                        }
+                        (h ? n1 : n0) = row_sum4(p, hi8, hi4);
+                    }
+                    // a column's norm, scale and its reciprocal go through LDS from
+                    // pair to pair (scl: two words per column after the norms)
+                    T *scl = nrm + cols;
+                    auto at = [&](int a) { return (a < 4 ? c0 : c1 - 4) + a; };
+                    auto put = [&](int a, const Col &v) {
+                        if ((gl & 3) == 0) {
+                            nrm[at(a)] = v.n;
+                            scl[2 * at(a)] = v.d;
+                            scl[2 * at(a) + 1] = v.id;
+                        }
+                    };
+                    auto get = [&](int a) { return Col{nrm[at(a)], scl[2 * at(a)], scl[2 * at(a) + 1]}; };
+                    auto wave_sync = [&]() {
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    };
+                    put(quad, Col{n0, T(1), T(1)});
+                    put(4 + quad, Col{n1, T(1), T(1)});
+                    auto step = [&](const int (&u)[4], const int (&v)[4]) {
+                        wave_sync();
+                        const int a = quad == 0 ? u[0] : quad == 1 ? u[1] : quad == 2 ? u[2] : u[3];
+                        const int b = quad == 0 ? v[0] : quad == 1 ? v[1] : quad == 2 ? v[2] : v[3];
+                        Col va = get(a), vb = get(b);
+                        rotate(u, v, va, vb);
+                        wave_sync();
+                        put(a, va);
+                        put(b, vb);
+                    };
+                    step({0, 2, 4, 6}, {1, 3, 5, 7});
+                    step({0, 1, 4, 5}, {2, 3, 6, 7});
+                    step({0, 1, 4, 5}, {3, 2, 7, 6});
+                    wave_sync();
+                    ca = get(quad);
+                    cb = get(4 + quad);
+                } else {
+                    ca.n = nrm[c0 + quad];
+                    cb.n = nrm[c1 + quad];
+                }
+                // round s: column q of c0 with column (q - s) % 4 of c1; the
+                // scalars of c1's columns move on by one quad per round
+                auto next = [&]() { cb = Col{dpp<kDppRor4>(cb.n), dpp<kDppRor4>(cb.d), dpp<kDppRor4>(cb.id)}; };
+                rotate({0, 1, 2, 3}, {4, 5, 6, 7}, ca, cb);
+                next();
+                rotate({0, 1, 2, 3}, {7, 4, 5, 6}, ca, cb);
+                next();
+                rotate({0, 1, 2, 3}, {6, 7, 4, 5}, ca, cb);
+                next();
+                rotate({0, 1, 2, 3}, {5, 6, 7, 4}, ca, cb);
+                next();
+                const T da[4] = {dpp<kDppBcast>(ca.d), dpp<kDppBcast + 4>(ca.d), dpp<kDppBcast + 8>(ca.d),
+                                 dpp<kDppBcast + 12>(ca.d)};
+                const T db[4] = {dpp<kDppBcast>(cb.d), dpp<kDppBcast + 4>(cb.d), dpp<kDppBcast + 8>(cb.d),
+                                 dpp<kDppBcast + 12>(cb.d)};
+                if ((gl & 3) == 0) {
+                    nrm[c0 + quad] = ca.n;
+                    nrm[c1 + quad] = cb.n;
+                }
+#pragma unroll
+                for (int j = 0; j < kJacBlk; ++j)
+#pragma unroll
+                    for (int e = 0; e < R; ++e) {
+                        pa[j * kp + 16 * e] = da[j] * x[j][e];
+                        pb[j * kp + 16 * e] = db[j] * x[kJacBlk + j][e];
+                    }
+            }
+            __syncthreads();
         }
+        // reduce the sweep's largest off-diagonal ratio over the workgroup
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
-            ss += __shfl_xor(ss, off, 64);
+            worst = fmaxf(worst, __shfl_xor(worst, off, 64));
         if (lane == 0)
-            sig[c] = sqrt(ss);
-    }
-    __syncthreads();
-    for (int c = tid; c < k; c += blockDim.x) {
-        int rk = 0;
-        for (int c2 = 0; c2 < k; ++c2)
-            rk += (sig[c2] > sig[c]) || (sig[c2] == sig[c] && c2 < c);
-        rank_of[c] = rk;
-    }
-    __syncthreads();
-    // numerical rank: singular values at the fp32 rounding floor of the
-    // largest one are zero (their vectors are noise, and 1/sigma would blow up)
-    if (tid == 0) {
-        double mx = 0.0;
-        for (int c = 0; c < k; ++c)
-            mx = fmax(mx, sig[c]);
-        sh_cut = kRankCutoff * mx;
-    }
-    __syncthreads();
-    for (int c = tid; c < k; c += blockDim.x)
-        if (sig[c] <= sh_cut)
-            sig[c] = 0.0;
-    __syncthreads();
-    for (int idx = tid; idx < KP * RP; idx += blockDim.x) {
-        Bu[idx] = 0.f;
-        Bv[idx] = 0.f;
-    }
-    __syncthreads();
-    for (int idx = tid; idx < k * k; idx += blockDim.x) {
-        const int c = idx / k, i = idx % k;
-        const int t = rank_of[c];
-        if (t < r) {
-            const double sg = sig[c];
-            const double u = sg > 0.0 ? static_cast<double>(A[c * kp + i]) / sg : 0.0;
-            Bu[i * RP + t] = static_cast<float>(u);
-            Bv[i * RP + t] = sg > 0.0 ? static_cast<float>(u / sg) : 0.f;
+            atomicMax(&sh_off, __float_as_uint(worst));
+        __syncthreads();
+        const float off = __uint_as_float(sh_off);
+        __syncthreads();
+        sweeps_used = sweep + 1;
+        last_off = off;
+        if (off <= static_cast<float>(tol))
+            break;
+        if (off < kJacCheck) {
+            // a sweep leaves about the square of what it met: the inner
+            // products themselves (matrix cores, about 2 us) tell whether
+            // this one was the last, instead of one more sweep
+            if (tid == 0)
+                sh_off = 0u;
+            __syncthreads();
+            const int nt = cols / 16 + (cols % 16 ? 1 : 0);
+            float w = 0.f;
+            for (int t = tid >> 6; t < nt * nt; t += nth >> 6) {
+                const int ti = t / nt, tj = t - ti * nt;
+                if (ti > tj)
+                    continue;
+                const int ci = ti * 16 + (lane & 15), cj = tj * 16 + (lane & 15);
+                const T *ai = A + min(ci, cols - 1) * kp + (lane >> 4), *aj = A + min(cj, cols - 1) * kp + (lane >> 4);
+                v4d g = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int e = 0; e < 16 * R; e += 4)
+                    g = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[e], aj[e], g, 0, 0, 0);
+                // D[i][j] in lane j + 16 (i % 4), element i / 4
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = ti * 16 + 4 * e + (lane >> 4);
+                    if (i < cj && cj < k) {
+                        const double prod = nrm[i] * nrm[cj];
+                        if (prod > 0.0)
+                            w = fmaxf(w, static_cast<float>(fabs(g[e]) * __builtin_amdgcn_rsq(prod)));
+                    }
+                }
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1)
+                w = fmaxf(w, __shfl_xor(w, o, 64));
+            if (lane == 0)
+                atomicMax(&sh_off, __float_as_uint(w));
+            __syncthreads();
+            const float left = __uint_as_float(sh_off);
+            __syncthreads();
+            if (left <= static_cast<float>(tol)) {
+                last_off = left;
+                break;
+            }
         }
     }
-    for (int c = tid; c < k; c += blockDim.x) {
-        const int t = rank_of[c];
-        if (t < r) {
-            const float sg = static_cast<float>(sig[c]);
-            s_out[t] = sg;
-            const float den = sg + tau;
-            d_out[t] = den != 0.f ? sg / den : 0.f;
-        }
-    }
+    jacobi_finish<T, kp>(J, A, k, KP, r, RP, tau, static_cast<float>(tol), sweeps_used, last_off, stamp);
 }
 
 // ---------------------------------------------------------------------------
@@ -1711,47 +2009,49 @@ void launch_tiles(const char *tag, std::vector<TileJob> jobs, hipStream_t st)
     }
 }
 
-// The Jacobi kernel for order k, by rows per lane (k rounded up to 32, over 8).
-template <typename T>
-using JacobiFn = void (*)(const Batch<JacJob>, int, int, int, int, float, T, int);
+using JacobiF64 = void (*)(const Batch<JacJob>, int, int, int, int, float, double, int);
+using JacobiF32 = void (*)(const Batch<JacJob>, int, int, int, int, float, float, int);
 
-// rows per lane: k rounded up to 8 V, divided by 8 (fp64: k <= 128)
-template <typename T>
-JacobiFn<T> jacobi_fn(int k)
+// fp64, k <= kJacobiF64MaxK: rows per lane of a row of 16
+JacobiF64 jacobi_f64(int k)
 {
-    switch (((k + 15) & ~15) / 8) {
-    case 2: return jacobi_kernel<T, 2>;
-    case 4: return jacobi_kernel<T, 4>;
-    case 6: return jacobi_kernel<T, 6>;
-    case 8: return jacobi_kernel<T, 8>;
-    case 10: return jacobi_kernel<T, 10>;
-    case 12: return jacobi_kernel<T, 12>;
-    case 14: return jacobi_kernel<T, 14>;
-    default: return jacobi_kernel<T, 16>;
-    }
-}
-template <>
-JacobiFn<float> jacobi_fn<float>(int k)
-{
-    switch (((k + 31) & ~31) / 8) {
-    case 4: return jacobi_kernel<float, 4>;
-    case 8: return jacobi_kernel<float, 8>;
-    case 12: return jacobi_kernel<float, 12>;
-    case 16: return jacobi_kernel<float, 16>;
-    case 20: return jacobi_kernel<float, 20>;
-    default: return jacobi_kernel<float, 24>;
+    switch ((k + 15) / 16) {
+    case 1: return jacobi_blocks_kernel<1>;
+    case 2: return jacobi_blocks_kernel<2>;
+    case 3: return jacobi_blocks_kernel<3>;
+    case 4: return jacobi_blocks_kernel<4>;
+    case 5: return jacobi_blocks_kernel<5>;
+    case 6: return jacobi_blocks_kernel<6>;
+    case 7: return jacobi_blocks_kernel<7>;
+    default: return jacobi_blocks_kernel<8>;
     }
 }
 
-// one 8-lane group per column pair of a round, at least 4 and at most 16 waves
+// fp32, beyond: rows per lane of a group of 8 (a multiple of 4)
+JacobiF32 jacobi_f32(int k) { return k <= 160 ? jacobi_pairs_kernel<20> : jacobi_pairs_kernel<24>; }
+
+// fp64: one row of 16 lanes per pair of blocks (16 pairs at most); four waves,
+// for what is not rounds.  fp32: one 8-lane group per column pair of a round.
 unsigned jacobi_threads(int k)
 {
-    const int npairs = (k + (k & 1)) / 2;
-    return 64u * static_cast<unsigned>(std::min<int64_t>(16, std::max<int64_t>(4, cdiv(npairs, 8))));
+    static_assert(kJacobiF64MaxK / kJacBlk / 2 * 16 <= 256, "a row of lanes per pair of blocks");
+    return k <= kJacobiF64MaxK ? 256u : 64u * static_cast<unsigned>(std::min<int64_t>(16, cdiv((k + 1) / 2, 8)));
 }
 
-// columns padded to a multiple of 8 V rows (32 in fp32, 16 in fp64), plus the squared norms
-size_t jacobi_lds(int k, size_t es) { return (static_cast<size_t>(k) * round_up(k, es == 8 ? 16 : 32) + k) * es; }
+// fp64: every block's columns, padded to 16 rows, and each column's squared
+// norm, scale and reciprocal scale; fp32: columns padded to 32 rows, and the
+// squared norms
+size_t jacobi_lds(int k)
+{
+    return k <= kJacobiF64MaxK ? static_cast<size_t>(jacobi_blocks(k) * kJacBlk) * (jacobi_pitch_f64(round_up(k, 16)) + 3) *
+                                     sizeof(double)
+                               : static_cast<size_t>(k) * (round_up(k, 32) + 1) * sizeof(float);
+}
+
+int jacobi_prepare(int k)
+{
+    return k <= kJacobiF64MaxK ? allow_lds(jacobi_f64(k), jacobi_lds(k)) : allow_lds(jacobi_f32(k), jacobi_lds(k));
+}
 
 // One tall-skinny product per job (opA * B), split-K through the job's
 // partial buffer `part` (nullptr: one split, straight into C).
@@ -2083,13 +2383,11 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         if (const char *e = std::getenv("ACSC_JACOBI_MAX_SWEEPS"))
             max_sweeps = std::max(1, std::min(kJacobiMaxSweeps, std::atoi(e)));
         if (k <= kJacobiF64MaxK)
-            launch_jobs("sc_jacobi", jacobi_fn<double>(k), jj, dim3(1), dim3(jacobi_threads(k)),
-                        jacobi_lds(k, sizeof(double)), st,
-                        k, KP, r, RP, tau, 1e-13, max_sweeps);
+            launch_jobs("sc_jacobi", jacobi_f64(k), jj, dim3(1), dim3(jacobi_threads(k)), jacobi_lds(k), st, k, KP, r,
+                        RP, tau, 1e-13, max_sweeps);
         else
-            launch_jobs("sc_jacobi", jacobi_fn<float>(k), jj, dim3(1), dim3(jacobi_threads(k)),
-                        jacobi_lds(k, sizeof(float)), st,
-                        k, KP, r, RP, tau, 1e-5f, max_sweeps);
+            launch_jobs("sc_jacobi", jacobi_f32(k), jj, dim3(1), dim3(jacobi_threads(k)), jacobi_lds(k), st, k, KP, r,
+                        RP, tau, 1e-5f, max_sweeps);
     }
     // U = Q Bu, V = Z Bv (first r columns)
     std::vector<orth::GemmReq> og;
@@ -2654,8 +2952,7 @@ int build_batched(int count, const sc_matrix *mats, acsc_dtype dt, float beta, i
     for (const Mat &m : all) {
         int rc = chol::prepare(m.D.KP);
         if (!rc)
-            rc = m.D.k <= kJacobiF64MaxK ? allow_lds(jacobi_fn<double>(m.D.k), jacobi_lds(m.D.k, sizeof(double)))
-                                         : allow_lds(jacobi_fn<float>(m.D.k), jacobi_lds(m.D.k, sizeof(float)));
+            rc = jacobi_prepare(m.D.k);
         if (rc)
             return rc;
     }

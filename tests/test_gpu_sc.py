@@ -378,6 +378,33 @@ def test_build_in_two_phases_equals_one_call(pk, fused, dtype):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("k", [1, 3, 5, 8, 9, 16, 17, 31, 44, 61, 80, 100, 113, 128, 129, 160, 161, 189])
+def test_ritz_step_at_every_block_count(pk, k):
+    """The Jacobi works on blocks of four columns (odd block counts and partial
+    blocks are padded with zero columns) up to order 128 and on column pairs
+    beyond: with k = n the Ritz step is the whole SVD of M, compared with
+    numpy's.  Bounds: fp32 M and Z = M^T Q, so about 1e-6 of the largest
+    singular value; the fp32 Jacobi stops at 1e-5."""
+    m, n = 260, k
+    g = torch.Generator().manual_seed(k)
+    q1, q2 = (torch.linalg.qr(torch.randn(s, k, generator=g, dtype=torch.float64))[0] for s in (m, n))
+    s0 = torch.exp(torch.linspace(math.log(10.0), 0.0, k, dtype=torch.float64)) if k > 1 else torch.tensor([3.0]).double()
+    if k > 4:
+        s0[2] = s0[1]                     # a repeated value: its vectors may be any basis
+    G = ((q1 * s0) @ q2.T).float()
+    M = torch.zeros(m, n, device="cuda")
+    ws = pk.workspace(m, n, k, 0, torch.float32)
+    U, s, V, d = pk.sc_build_prior(G.cuda(), M, k, 0.0, 0.0, 0, 1, seed=1, ws=ws)
+    torch.cuda.synchronize()
+    pk.sc_build_status([ws])
+    ref = np.linalg.svd(G.double().numpy(), compute_uv=False)
+    assert np.max(np.abs(_np(s) - ref)) <= 2e-5 * ref[0]
+    tol = 2e-4 if k > 128 else 2e-5
+    assert osp.rel_fro(_np(U) * _np(s) @ _np(V).T, G.double().numpy()) <= tol
+    for B in (_np(U), _np(V)):
+        assert np.max(np.abs(B.T @ B - np.eye(k))) <= tol
+
+
 @pytest.mark.parametrize("r,p", [(16, 8), (130, 16)])
 def test_build_status_reports_a_sweep_cap_and_a_missing_subspace_phase(pk, r, p, monkeypatch):
     """The Rayleigh-Ritz Jacobi (fp64 for k <= 128, fp32 above) reports its
