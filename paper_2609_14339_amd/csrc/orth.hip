@@ -18,6 +18,24 @@ namespace {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
+// Four floats of a row of which `avail` (any number) are left; the rest read
+// as zero.  The row needs element alignment only: priors of a rank that is no
+// multiple of 4 have such rows.
+struct __attribute__((packed, aligned(4))) F4 {
+    float v[4];
+};
+template <bool VEC>   // 16-byte aligned rows, `avail` a multiple of 4
+__device__ __forceinline__ float4 load4(const float *p, int avail)
+{
+    if constexpr (VEC)
+        return avail > 0 ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (avail >= 4) {
+        const F4 x = *reinterpret_cast<const F4 *>(p);
+        return make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
+    }
+    return make_float4(avail > 0 ? p[0] : 0.f, avail > 1 ? p[1] : 0.f, avail > 2 ? p[2] : 0.f, 0.f);
+}
+
 constexpr int kRows = 128;            // rows of A per workgroup
 constexpr int kKC = 32;               // depth of one chunk
 constexpr int kYP = kKC + 1;          // A chunk pitch in floats (column reads conflict-free)
@@ -51,7 +69,7 @@ struct Lds {
     static constexpr int FLOATS = MAIN > STAGE ? MAIN : STAGE;
 };
 
-template <int NT, bool TRI>
+template <int NT, bool TRI, bool VEC>
 __global__ __launch_bounds__(256) void tall_small_kernel(const Batch jb)
 {
     using L = Lds<NT>;
@@ -83,8 +101,8 @@ __global__ __launch_bounds__(256) void tall_small_kernel(const Batch jb)
             const int idx = tid + 256 * u;
             const int r = idx >> 3, c = k0 + (idx & 7) * 4;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (row0 + r < rows && c < K)
-                v = *reinterpret_cast<const float4 *>(A + static_cast<int64_t>(row0 + r) * lda + c);
+            if (row0 + r < rows)
+                v = load4<VEC>(A + static_cast<int64_t>(row0 + r) * lda + c, K - c);
             yr[u] = v;
         }
 #pragma unroll
@@ -226,10 +244,15 @@ void launch(const char *tag, const std::vector<Job> &jobs, hipStream_t st)
             gx = std::max(gx, (b.j[i].rows + kRows - 1) / kRows);
         }
         // run() and gemm() each make jobs of one kind (triangular B or not)
+        bool vec = true;
+        for (int i = 0; i < b.count; ++i)
+            vec = vec && aligned(b.j[i].A, 16) && b.j[i].lda % 4 == 0 && b.j[i].K % 4 == 0;
         if (b.j[0].tri)
-            ACSC_LAUNCH(tag, (tall_small_kernel<NT, true>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+            ACSC_LAUNCH(tag, (tall_small_kernel<NT, true, true>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+        else if (vec)
+            ACSC_LAUNCH(tag, (tall_small_kernel<NT, false, true>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
         else
-            ACSC_LAUNCH(tag, (tall_small_kernel<NT, false>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+            ACSC_LAUNCH(tag, (tall_small_kernel<NT, false, false>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
     }
 }
 
@@ -269,7 +292,7 @@ struct InnerBatch {
     InnerJob j[kMaxJobs];
 };
 
-template <int NT>
+template <int NT, bool VEC>
 __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
 {
     constexpr int W = NT * 32;                 // staged row width (floats)
@@ -304,8 +327,7 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
             const int gr = rb + rr;
             float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
             if (idx < CV && gr < r1) {
-                if (c < NA)
-                    a = *reinterpret_cast<const float4 *>(J.A + static_cast<int64_t>(gr) * J.lda + c);
+                a = load4<VEC>(J.A + static_cast<int64_t>(gr) * J.lda + c, NA - c);
                 if (c < NB)
                     b = *reinterpret_cast<const float4 *>(J.B + static_cast<int64_t>(gr) * J.ldb + c);
             }
@@ -344,7 +366,7 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
         }
     }
     // D[i][j] in lane j + 32 ((i / 4) % 2), element 4 (i / 8) + i % 4
-    float *pp = J.part + static_cast<int64_t>(blockIdx.x) * W * W;
+    float *pp = J.part + static_cast<int64_t>(blockIdx.x) * NA * NB;
 #pragma unroll
     for (int u = 0; u < TPW; ++u) {
         const int t = wave + 4 * u;
@@ -352,8 +374,9 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
             const int ti = t / NT, tj = t % NT;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int i = 32 * ti + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-                pp[i * W + 32 * tj + (lane & 31)] = acc[u][e];
+                const int i = 32 * ti + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3), j = 32 * tj + (lane & 31);
+                if (i < NA && j < NB)
+                    pp[i * NB + j] = acc[u][e];
             }
         }
     }
@@ -361,7 +384,7 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
 
 struct InnerRedJob {
     const float *part;
-    int blocks, NA, NB, W;
+    int blocks, NA, NB;
     float *C;
     int64_t ldc;
 };
@@ -378,8 +401,8 @@ __global__ __launch_bounds__(256) void tall_inner_reduce_kernel(const InnerRedBa
     if (idx >= J.NA * J.NB)
         return;
     const int i = idx / J.NB, j = idx - (idx / J.NB) * J.NB;
-    const int64_t stride = static_cast<int64_t>(J.W) * J.W;
-    const float *p = J.part + i * J.W + j;
+    const int64_t stride = static_cast<int64_t>(J.NA) * J.NB;
+    const float *p = J.part + idx;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     int b = 0;
     for (; b + 4 <= J.blocks; b += 4) {
@@ -408,7 +431,13 @@ void launch_inner(const char *tag, const std::vector<InnerJob> &jobs, const std:
             gx = std::max(gx, b.j[i].blocks);
             rx = std::max(rx, (rb.j[i].NA * rb.j[i].NB + 255) / 256);
         }
-        ACSC_LAUNCH(tag, tall_inner_kernel<NT>, dim3(gx, 1, b.count), dim3(256), 0, st, b);
+        bool vec = true;
+        for (int i = 0; i < b.count; ++i)
+            vec = vec && aligned(b.j[i].A, 16) && b.j[i].lda % 4 == 0 && b.j[i].NA % 4 == 0;
+        if (vec)
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, true>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+        else
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, false>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
         ACSC_LAUNCH("sc_inner_reduce", tall_inner_reduce_kernel, dim3(rx, 1, rb.count), dim3(256), 0, st, rb);
     }
 }
@@ -433,12 +462,21 @@ int run(const char *tag, const std::vector<Req> &reqs, int KP, hipStream_t st)
     return launch_all(tag, jobs, st);
 }
 
+namespace {
+
 bool gemm_supported(const GemmReq &q)
 {
-    return aligned(q.A, 16) && aligned(q.B, 16) && q.lda % 4 == 0 && q.ldb % 4 == 0 && q.K % 4 == 0 &&
-           q.N % 4 == 0 && q.K >= 1 && q.K <= SC_KMAX && q.N >= 1 && q.N <= SC_KMAX && q.nwrite <= SC_KMAX &&
-           q.lda >= q.K && q.ldb >= q.N && q.ldc >= q.nwrite;
+    return aligned(q.A, 4) && aligned(q.B, 16) && q.ldb % 4 == 0 && q.N % 4 == 0 && q.K >= 1 && q.K <= SC_KMAX &&
+           q.N >= 1 && q.N <= SC_KMAX && q.nwrite <= SC_KMAX && q.lda >= q.K && q.ldb >= q.N && q.ldc >= q.nwrite;
 }
+
+bool inner_supported(const InnerReq &q)
+{
+    return aligned(q.A, 4) && aligned(q.B, 16) && q.ldb % 4 == 0 && q.NB % 4 == 0 && q.NA >= 1 && q.NA <= SC_KMAX &&
+           q.NB >= 1 && q.NB <= SC_KMAX && q.lda >= q.NA && q.ldb >= q.NB && q.ldc >= q.NB && q.part_blocks >= 1;
+}
+
+}  // namespace
 
 int gemm(const char *tag, const std::vector<GemmReq> &reqs, hipStream_t st)
 {
@@ -453,15 +491,6 @@ int gemm(const char *tag, const std::vector<GemmReq> &reqs, hipStream_t st)
     return launch_all(tag, jobs, st);
 }
 
-bool inner_supported(const InnerReq &q)
-{
-    const int64_t W = (std::max(q.NA, q.NB) + 31) / 32 * 32;
-    return aligned(q.A, 16) && aligned(q.B, 16) && q.lda % 4 == 0 && q.ldb % 4 == 0 && q.NA % 4 == 0 &&
-           q.NB % 4 == 0 && q.NA >= 1 && q.NA <= SC_KMAX && q.NB >= 1 && q.NB <= SC_KMAX && q.lda >= q.NA &&
-           q.ldb >= q.NB && q.ldc >= q.NB &&
-           static_cast<int64_t>(q.part_blocks) * q.NA * q.NB >= W * W;   // room for one partial block
-}
-
 int inner(const char *tag, const std::vector<InnerReq> &reqs, hipStream_t st)
 {
     int np = 32;
@@ -472,7 +501,7 @@ int inner(const char *tag, const std::vector<InnerReq> &reqs, hipStream_t st)
         np = std::max(np, std::max(q.NA, q.NB));
         total += std::max(q.rows, 0);
     }
-    const int NT = (np + 31) / 32, W = NT * 32;
+    const int NT = (np + 31) / 32;
     // one row count per block across the batch (about two workgroups per CU),
     // raised where a matrix's partial buffer holds fewer blocks
     const int64_t rpb_batch = std::max<int64_t>(32, (total + 511) / 512 + 31) / 32 * 32;
@@ -481,14 +510,11 @@ int inner(const char *tag, const std::vector<InnerReq> &reqs, hipStream_t st)
     for (const InnerReq &q : reqs) {
         if (q.rows < 1)
             continue;
-        const int64_t cap = static_cast<int64_t>(q.part_blocks) * q.NA * q.NB / (static_cast<int64_t>(W) * W);
-        if (cap < 1)
-            return set_error(ACSC_EINVAL, "tall inner product: partial buffer too small");
-        int64_t rpb = std::max<int64_t>(rpb_batch, (q.rows + cap - 1) / cap);
+        int64_t rpb = std::max<int64_t>(rpb_batch, (q.rows + q.part_blocks - 1) / q.part_blocks);
         rpb = (rpb + 31) / 32 * 32;
         const int blocks = static_cast<int>((q.rows + rpb - 1) / rpb);
         jobs.push_back(InnerJob{q.A, q.lda, q.B, q.ldb, q.rows, q.NA, q.NB, static_cast<int>(rpb), blocks, q.part});
-        red.push_back(InnerRedJob{q.part, blocks, q.NA, q.NB, W, q.C, q.ldc});
+        red.push_back(InnerRedJob{q.part, blocks, q.NA, q.NB, q.C, q.ldc});
     }
     if (jobs.empty())
         return ACSC_OK;

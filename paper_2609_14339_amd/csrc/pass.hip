@@ -646,14 +646,8 @@ __global__ __launch_bounds__(512)
         }
 }
 
-// C[i, c] = sum over splits of part[s][i, c] (NP columns, float4 when aligned).
-struct RedJob {
-    const float *part;
-    int64_t split_stride;
-    float *C;
-    int64_t ldc;
-    int M, NP, splits;
-};
+// C[i, c] = sum over splits of part[s][i, c].
+using RedJob = Partials;
 struct RedBatch {
     int count;
     RedJob j[kMaxJobs];
@@ -1251,6 +1245,21 @@ std::vector<size_t> longest_first(const std::vector<Req> &reqs)
 
 }  // namespace
 
+void add_partials(const std::vector<Partials> &red, hipStream_t st)
+{
+    for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
+        RedBatch b{};
+        b.count = static_cast<int>(std::min<size_t>(kMaxJobs, red.size() - c0));
+        int64_t tot = 1;
+        for (int i = 0; i < b.count; ++i) {
+            b.j[i] = red[c0 + i];
+            tot = std::max<int64_t>(tot, static_cast<int64_t>(b.j[i].M) * (b.j[i].NP / 4));
+        }
+        const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(tot, 256), 8192));
+        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
+    }
+}
+
 std::vector<int> plan_splits(const std::vector<Req> &reqs)
 {
     std::vector<int> out(reqs.size(), 1);
@@ -1294,7 +1303,6 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
     std::vector<int> vsplits, vchunk;
     std::vector<RedJob> red;
     int gx = 1;
-    int64_t rtot = 1;
     const std::vector<int> nsplit = plan_splits(reqs);
     for (size_t oi : order) {
         const Req &q = reqs[oi];
@@ -1305,7 +1313,6 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
             splits_out[oi] = splits;
         if (splits > 1 && !splits_out) {
             red.push_back(RedJob{q.part, ss, q.C, q.ldc, q.M, NP, splits});
-            rtot = std::max<int64_t>(rtot, static_cast<int64_t>(q.M) * (NP / 4));
         }
         if (q.avec) {
             vq.push_back(&q);
@@ -1355,17 +1362,9 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
             const int64_t r0 = static_cast<int64_t>(js[i].nrb - h) * kBM;
             red.push_back(RedJob{q.part + r0 * NP, static_cast<int64_t>(q.M) * NP, q.C + r0 * q.ldc, q.ldc,
                                  static_cast<int>(q.M - r0), NP, 2});
-            rtot = std::max<int64_t>(rtot, (q.M - r0) * (NP / 4));
         }
     }
-    for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
-        RedBatch b{};
-        b.count = static_cast<int>(std::min<size_t>(kMaxJobs, red.size() - c0));
-        for (int i = 0; i < b.count; ++i)
-            b.j[i] = red[c0 + i];
-        const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(rtot, 256), 8192));
-        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
-    }
+    add_partials(red, st);
     return ACSC_OK;
 }
 
@@ -1399,7 +1398,6 @@ int ema_run(const char *tag, const std::vector<EmaReq> &reqs, float a, float b, 
         order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return reqs[a].n > reqs[b].n; });
     std::vector<RedJob> red;
-    int64_t rtot = 1;
     for (size_t c0 = 0; c0 < order.size(); c0 += kMaxJobs) {
         const size_t cnt = std::min<size_t>(kMaxJobs, order.size() - c0);
         std::vector<JobShape> js;
@@ -1438,17 +1436,9 @@ int ema_run(const char *tag, const std::vector<EmaReq> &reqs, float a, float b, 
             const int64_t r0 = static_cast<int64_t>(js[i].nrb - h) * kBM;
             red.push_back(RedJob{q.part + r0 * NP, static_cast<int64_t>(q.m) * NP, q.C + r0 * q.ldc, q.ldc,
                                  static_cast<int>(q.m - r0), NP, 2});
-            rtot = std::max<int64_t>(rtot, (q.m - r0) * (NP / 4));
         }
     }
-    for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
-        RedBatch rb{};
-        rb.count = static_cast<int>(std::min<size_t>(kMaxJobs, red.size() - c0));
-        for (int i = 0; i < rb.count; ++i)
-            rb.j[i] = red[c0 + i];
-        const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(rtot, 256), 8192));
-        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, rb.count), dim3(256), 0, st, rb);
-    }
+    add_partials(red, st);
     return ACSC_OK;
 }
 

@@ -14,6 +14,7 @@
 #include "sc_blend.h"
 #include "sc_chol.h"
 #include "sc_orth.h"
+#include "sc_f32.h"
 
 #include <algorithm>
 #include <utility>
@@ -28,9 +29,6 @@ typedef float nf4 __attribute__((ext_vector_type(4)));
 typedef unsigned int nu4 __attribute__((ext_vector_type(4)));
 
 constexpr int kKMax = SC_KMAX;
-constexpr int kBM = 64;   // rows of the output per workgroup in the tall GEMM
-constexpr int kBK = 32;   // depth of one K step
-constexpr int kNTMax = kKMax / 16;
 // Singular values of the prior at or below this fraction of the largest are
 // returned as zero (numerical rank of an fp32 subspace iteration).
 constexpr double kRankCutoff = 1e-5;
@@ -67,161 +65,6 @@ template <>
 __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <>
 __device__ __forceinline__ uint16_t from_f32<uint16_t>(float v) { return f32_to_bf16(v); }
-
-template <typename T>
-__device__ __forceinline__ T cvt_ct(float v) { return from_f32<T>(v); }
-
-// ---------------------------------------------------------------------------
-// Tall-skinny GEMM with split-K:
-//   C[s][i, c] = sum_{k in split s} opA[i, k] * B[k, c]
-// opA = A (A is [M, K] row-major) or A^T (A is stored [K, M] row-major).
-// B is fp32 [K, ldb]; columns >= nvalid read as zero.  C gets `nwrite`
-// columns.  With one split the result goes straight to C (which may then be
-// A itself for a square right factor: each workgroup reads all of its rows
-// before it writes them).
-// A of type float runs on v_mfma_f32_16x16x4f32, bf16 on
-// v_mfma_f32_16x16x32_bf16; B is converted to A's type in LDS.
-// ---------------------------------------------------------------------------
-template <typename TA>
-struct GemmLds;
-template <>
-struct GemmLds<uint16_t> {
-    static constexpr int APITCH = kBK + 8;   // 80-byte rows keep 16-byte alignment
-    static constexpr int BPITCH = kBK + 8;
-};
-template <>
-struct GemmLds<float> {
-    static constexpr int APITCH = kBK + 1;
-    static constexpr int BPITCH = kBK + 1;
-};
-
-template <typename TA, typename TO>
-struct GemmJob {
-    const TA *A;
-    int64_t lda;
-    const float *B;
-    int64_t ldb;
-    TO *C;
-    int64_t ldc, split_stride;
-    int M, K, nvalid, nwrite, kchunk, splits;
-    uint16_t *Ct16;
-    int64_t ldct;
-};
-
-template <typename TA, bool TRANS, typename TO>
-__global__ __launch_bounds__(256) void gemm_tall_kernel(const Batch<GemmJob<TA, TO>> jb)
-{
-    const GemmJob<TA, TO> &J = jb.j[blockIdx.z];
-    if (static_cast<int>(blockIdx.y) >= J.splits || static_cast<int>(blockIdx.x) * kBM >= J.M)
-        return;
-    const TA *A = J.A;
-    const int64_t lda = J.lda;
-    const float *B = J.B;
-    const int64_t ldb = J.ldb;
-    TO *C = J.C;
-    const int64_t ldc = J.ldc, split_stride = J.split_stride;
-    const int M = J.M, K = J.K, nvalid = J.nvalid, nwrite = J.nwrite, kchunk = J.kchunk;
-    uint16_t *Ct16 = J.Ct16;
-    const int64_t ldct = J.ldct;
-    using L = GemmLds<TA>;
-    __shared__ __attribute__((aligned(16))) TA As[kBM * L::APITCH];
-    __shared__ __attribute__((aligned(16))) TA Bs[kKMax * L::BPITCH];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int row0 = blockIdx.x * kBM;
-    const int kbeg = blockIdx.y * kchunk;
-    const int kend = min(K, kbeg + kchunk);
-    const int NP = static_cast<int>(round_up(nwrite, 16));
-    const int NT = NP / 16;
-
-    f32x4 acc[kNTMax];
-#pragma unroll
-    for (int t = 0; t < kNTMax; ++t)
-        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    for (int k0 = kbeg; k0 < kend; k0 += kBK) {
-        __syncthreads();
-        // A tile -> As[i][kk]
-        if (!TRANS) {
-            const int i = tid >> 2;
-            const int c0 = (tid & 3) * 8;
-            const int gi = row0 + i;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int gk = k0 + c0 + e;
-                TA v = 0;
-                if (gi < M && gk < kend)
-                    v = A[static_cast<int64_t>(gi) * lda + gk];
-                As[i * L::APITCH + c0 + e] = v;
-            }
-        } else {
-            const int kk = tid >> 3;
-            const int i0 = (tid & 7) * 8;
-            const int gk = k0 + kk;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int gi = row0 + i0 + e;
-                TA v = 0;
-                if (gi < M && gk < kend)
-                    v = A[static_cast<int64_t>(gk) * lda + gi];
-                As[(i0 + e) * L::APITCH + kk] = v;
-            }
-        }
-        // B tile -> Bs[c][kk]
-        for (int idx = tid; idx < kBK * NP; idx += 256) {
-            const int kk = idx / NP;
-            const int c = idx - kk * NP;
-            const int gk = k0 + kk;
-            float v = 0.f;
-            if (gk < kend && c < nvalid)
-                v = B[static_cast<int64_t>(gk) * ldb + c];
-            Bs[c * L::BPITCH + kk] = cvt_ct<TA>(v);
-        }
-        __syncthreads();
-        const int ar = wave * 16 + (lane & 15);
-        if constexpr (sizeof(TA) == 2) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&As[ar * L::APITCH + (lane >> 4) * 8]);
-#pragma unroll
-            for (int t = 0; t < kNTMax; ++t) {
-                if (t < NT) {
-                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(
-                        &Bs[(t * 16 + (lane & 15)) * L::BPITCH + (lane >> 4) * 8]);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int s4 = 0; s4 < kBK / 4; ++s4) {
-                const float a = As[ar * L::APITCH + s4 * 4 + (lane >> 4)];
-#pragma unroll
-                for (int t = 0; t < kNTMax; ++t) {
-                    if (t < NT) {
-                        const float b = Bs[(t * 16 + (lane & 15)) * L::BPITCH + s4 * 4 + (lane >> 4)];
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[t], 0, 0, 0);
-                    }
-                }
-            }
-        }
-    }
-    TO *Cs = C + static_cast<int64_t>(blockIdx.y) * split_stride;
-#pragma unroll
-    for (int t = 0; t < kNTMax; ++t) {
-        if (t < NT) {
-            const int col = t * 16 + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = row0 + wave * 16 + (lane >> 4) * 4 + e;
-                if (row < M && col < nwrite) {
-                    Cs[static_cast<int64_t>(row) * ldc + col] = from_f32<TO>(acc[t][e]);
-                    if (Ct16)
-                        Ct16[static_cast<int64_t>(col) * ldct + row] = f32_to_bf16(acc[t][e]);
-                }
-            }
-        }
-    }
-}
 
 // Anchor EMA with a bf16 shadow for the streaming passes (one thread per 8
 // consecutive elements of a row; 16-byte accesses when rows are aligned):
@@ -305,59 +148,6 @@ __global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob<GT>>
                 M16[tile_at(i, j0 + e, ntc)] = f32_to_bf16(x);
             }
         }
-    }
-}
-
-// C[i, c] = sum_s P[s][i, c] for c < nwrite (P has row stride ldp).
-template <typename TO>
-struct ReduceJob {
-    const float *P;
-    int64_t ldp, split_stride;
-    int splits, M, nwrite;
-    TO *C;
-    int64_t ldc;
-};
-
-template <typename TO>
-__global__ __launch_bounds__(256) void reduce_splits_kernel(const Batch<ReduceJob<TO>> jb)
-{
-    const ReduceJob<TO> &J = jb.j[blockIdx.z];
-    const float *P = J.P;
-    const int64_t ldp = J.ldp, split_stride = J.split_stride, ldc = J.ldc;
-    const int splits = J.splits, M = J.M, nwrite = J.nwrite;
-    TO *C = J.C;
-    if constexpr (sizeof(TO) == 4) {
-        // four columns per thread when every row is 16-byte aligned
-        if ((nwrite & 3) == 0 && (ldp & 3) == 0 && (ldc & 3) == 0 && (split_stride & 3) == 0 &&
-            (reinterpret_cast<uintptr_t>(P) & 15) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
-            const int nq = nwrite >> 2;
-            const int64_t total = static_cast<int64_t>(M) * nq;
-            for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
-                 idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-                const int64_t i = idx / nq;
-                const int c = static_cast<int>(idx - i * nq) * 4;
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                for (int p = 0; p < splits; ++p) {
-                    const float4 v = *reinterpret_cast<const float4 *>(P + p * split_stride + i * ldp + c);
-                    acc.x += v.x;
-                    acc.y += v.y;
-                    acc.z += v.z;
-                    acc.w += v.w;
-                }
-                *reinterpret_cast<float4 *>(C + i * ldc + c) = acc;
-            }
-            return;
-        }
-    }
-    const int64_t total = static_cast<int64_t>(M) * nwrite;
-    for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
-         idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int64_t i = idx / nwrite;
-        const int c = static_cast<int>(idx - i * nwrite);
-        float s = 0.f;
-        for (int p = 0; p < splits; ++p)
-            s += P[p * split_stride + i * ldp + c];
-        C[i * ldc + c] = from_f32<TO>(s);
     }
 }
 
@@ -1556,11 +1346,6 @@ __global__ __launch_bounds__(256) void pad_convert_kernel(const Batch<PadJob<CT>
     }
 }
 
-// ---------------------------------------------------------------------------
-// Fused correction pass: out = alpha * G + (1 - alpha) * P V^T for a 64 x 64
-// tile, with P [m, RP] and Vc [n, RP] in the compute type (RP a multiple of
-// 32, zero padded).  Four waves, each a 32 x 32 quarter of the tile.
-// ---------------------------------------------------------------------------
 template <typename GT>
 struct BlendJob {
     const GT *G;
@@ -1586,95 +1371,6 @@ __device__ __forceinline__ void blend_out(const BlendJob<GT> &J, int64_t o, floa
     } else {
         J.out[o] = from_f32<GT>(gp);
     }
-}
-
-template <typename GT, int MODE>
-__global__ __launch_bounds__(256) void blend_kernel(const Batch<BlendJob<GT>> jb, int RP, float alpha,
-                                                    const blend::AdamArgs ad)
-{
-    constexpr bool ADAM = MODE == blend::kAdam;
-    const BlendJob<GT> &J = jb.j[blockIdx.z];
-    const GT *G = J.G;
-    const int m = J.m, n = J.n;
-    const GT *P = J.P, *Vc = J.Vc;
-    if (static_cast<int>(blockIdx.x) * 64 >= n || static_cast<int>(blockIdx.y) * 64 >= m)
-        return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char bsm[];
-    constexpr int PAD = sizeof(GT) == 2 ? 8 : 1;
-    const int pitch = RP + PAD;
-    GT *Ps = reinterpret_cast<GT *>(bsm);
-    GT *Vs = Ps + kBM * pitch;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col0 = blockIdx.x * 64, row0 = blockIdx.y * 64;
-    for (int idx = tid; idx < 64 * RP; idx += 256) {
-        const int rr = idx / RP, c = idx % RP;
-        const int gi = row0 + rr, gj = col0 + rr;
-        Ps[rr * pitch + c] = gi < m ? P[static_cast<int64_t>(gi) * RP + c] : GT(0);
-        Vs[rr * pitch + c] = gj < n ? Vc[static_cast<int64_t>(gj) * RP + c] : GT(0);
-    }
-    __syncthreads();
-    const int wr = wave >> 1, wc = wave & 1;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (sizeof(GT) == 2) {
-        for (int k0 = 0; k0 < RP; k0 += 32) {
-            bf16x8 af[2], bfr[2];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                af[a] = *reinterpret_cast<const bf16x8 *>(
-                    &Ps[(wr * 32 + a * 16 + (lane & 15)) * pitch + k0 + (lane >> 4) * 8]);
-                bfr[a] = *reinterpret_cast<const bf16x8 *>(
-                    &Vs[(wc * 32 + a * 16 + (lane & 15)) * pitch + k0 + (lane >> 4) * 8]);
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-        }
-    } else {
-        for (int k0 = 0; k0 < RP; k0 += 4) {
-            float af[2], bfr[2];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                af[a] = Ps[(wr * 32 + a * 16 + (lane & 15)) * pitch + k0 + (lane >> 4)];
-                bfr[a] = Vs[(wc * 32 + a * 16 + (lane & 15)) * pitch + k0 + (lane >> 4)];
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[a], bfr[b], acc[a][b], 0, 0, 0);
-        }
-    }
-    const float oma = 1.0f - alpha;
-    const float cf = ADAM ? *ad.coef : 1.0f;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int col = col0 + wc * 32 + b * 16 + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = row0 + wr * 32 + a * 16 + (lane >> 4) * 4 + e;
-                if (row < m && col < n) {
-                    const int64_t o = static_cast<int64_t>(row) * n + col;
-                    if constexpr (MODE == blend::kFeedback) {
-                        // out = P V^T as stored; the memory takes M - out
-                        const GT ov = from_f32<GT>(acc[a][b][e]);
-                        J.out[o] = ov;
-                        J.E[o] = J.E[o] - to_f32<GT>(ov);
-                    } else {
-                        const float g = to_f32<GT>(G[o]);
-                        blend_out<ADAM>(J, o, blend_step(g, acc[a][b][e], alpha, oma), cf, ad);
-                    }
-                }
-            }
-        }
 }
 
 // ---------------------------------------------------------------------------
@@ -1868,15 +1564,15 @@ struct Carve {
     }
 };
 
+// Most k pieces of an fp32 product with M rows (two 64-row workgroups per CU,
+// 256 deep at least): what the workspaces have room for.
 int split_count(int64_t Mdim, int64_t Kdim)
 {
-    const int64_t mb = cdiv(Mdim, kBM);
+    const int64_t mb = cdiv(Mdim, 64);
     int64_t s = cdiv(512, mb);
     s = std::min<int64_t>(s, std::max<int64_t>(1, Kdim / 256));
     return static_cast<int>(std::max<int64_t>(1, s));
 }
-
-int64_t split_chunk(int64_t Kdim, int splits) { return round_up(cdiv(Kdim, splits), kBK); }
 
 // Most Gram partial blocks a matrix of this many rows may be split into.
 int gram_blocks_max(int64_t rows) { return static_cast<int>(std::min<int64_t>(128, cdiv(rows, kGRows))); }
@@ -2051,58 +1747,6 @@ size_t jacobi_lds(int k)
 int jacobi_prepare(int k)
 {
     return k <= kJacobiF64MaxK ? allow_lds(jacobi_f64(k), jacobi_lds(k)) : allow_lds(jacobi_f32(k), jacobi_lds(k));
-}
-
-// One tall-skinny product per job (opA * B), split-K through the job's
-// partial buffer `part` (nullptr: one split, straight into C).
-template <typename TA, typename TO>
-struct GemmReq {
-    const TA *A;
-    int64_t lda;
-    const float *B;
-    int64_t ldb;
-    TO *C;
-    int64_t ldc;
-    int M, K, nvalid, nwrite;
-    float *part;
-    uint16_t *Ct16;
-    int64_t ldct;
-};
-
-template <typename TA, bool TRANS, typename TO>
-void tall_gemm(const char *tag, const std::vector<GemmReq<TA, TO>> &reqs, hipStream_t st)
-{
-    std::vector<GemmJob<TA, TO>> direct;
-    std::vector<GemmJob<TA, float>> split;
-    std::vector<ReduceJob<TO>> red;
-    int gx = 1, gy = 1, sx = 1, sy = 1;
-    int64_t rtot = 1;
-    for (const auto &q : reqs) {
-        const int NP = static_cast<int>(round_up(q.nwrite, 16));
-        int splits = q.part ? split_count(q.M, q.K) : 1;
-        const int64_t chunk = split_chunk(q.K, splits);
-        splits = static_cast<int>(cdiv(q.K, chunk));
-        const int mb = static_cast<int>(cdiv(q.M, kBM));
-        if (splits == 1) {
-            direct.push_back(GemmJob<TA, TO>{q.A, q.lda, q.B, q.ldb, q.C, q.ldc, 0, q.M, q.K, q.nvalid, q.nwrite,
-                                             static_cast<int>(chunk), 1, q.Ct16, q.ldct});
-            gx = std::max(gx, mb);
-        } else {
-            const int64_t ss = static_cast<int64_t>(q.M) * NP;
-            split.push_back(GemmJob<TA, float>{q.A, q.lda, q.B, q.ldb, q.part, NP, ss, q.M, q.K, q.nvalid, NP,
-                                               static_cast<int>(chunk), splits, nullptr, 0});
-            red.push_back(ReduceJob<TO>{q.part, NP, ss, splits, q.M, q.nwrite, q.C, q.ldc});
-            sx = std::max(sx, mb);
-            sy = std::max(sy, splits);
-            rtot = std::max<int64_t>(rtot, static_cast<int64_t>(q.M) * q.nwrite);
-        }
-    }
-    if (!direct.empty())
-        launch_jobs(tag, gemm_tall_kernel<TA, TRANS, TO>, direct, dim3(gx, gy), dim3(256), 0, st);
-    if (!split.empty()) {
-        launch_jobs(tag, gemm_tall_kernel<TA, TRANS, float>, split, dim3(sx, sy), dim3(256), 0, st);
-        launch_jobs("sc_split_reduce", reduce_splits_kernel<TO>, red, dim3(grid1d(rtot)), dim3(256), 0, st);
-    }
 }
 
 // Per-matrix state of a batched call.
@@ -2299,7 +1943,7 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         }
     }
     // one pass Y = M Z  /  Z = M^T Y over every EMA (bf16 shadow on matrix cores, or fp32);
-    // `splits` takes the partials that the bf16 products are left in
+    // `splits` takes the partials that the products are left in
     auto reqs16 = [&](bool mz) {
         std::vector<pass::Req> q;
         for (auto &m : ms) {
@@ -2312,26 +1956,20 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         }
         return q;
     };
+    auto reqs32 = [&](bool mz) {
+        std::vector<f32::PassReq> q;
+        for (auto &m : ms) {
+            const int M = mz ? m.D.m : m.D.n, K = mz ? m.D.n : m.D.m;
+            q.push_back(f32::PassReq{m.in->M, m.D.n, mz ? m.pw.Z : m.pw.Y, KP, mz ? m.pw.Y : m.pw.Z, KP, M, K, k, KP,
+                                     m.pw.part, split_count(M, K)});
+        }
+        return q;
+    };
     std::vector<int> splits(ms.size(), 1);
     auto pass = [&](bool mz) {
-        if (use16) {
+        if (use16)
             return pass::run(mz ? "sc_pass_mz" : "sc_pass_mtq", !mz, reqs16(mz), st, splits.data());
-        } else {
-            std::vector<GemmReq<float, float>> q;
-            for (auto &m : ms) {
-                if (mz)
-                    q.push_back(GemmReq<float, float>{m.in->M, m.D.n, m.pw.Z, KP, m.pw.Y, KP, m.D.m, m.D.n, k, KP,
-                                                      m.pw.part, nullptr, 0});
-                else
-                    q.push_back(GemmReq<float, float>{m.in->M, m.D.n, m.pw.Y, KP, m.pw.Z, KP, m.D.n, m.D.m, k, KP,
-                                                      m.pw.part, nullptr, 0});
-            }
-            if (mz)
-                tall_gemm<float, false, float>("sc_pass_mz", q, st);
-            else
-                tall_gemm<float, true, float>("sc_pass_mtq", q, st);
-            return ACSC_OK;
-        }
+        return f32::pass(mz ? "sc_pass_mz" : "sc_pass_mtq", !mz, reqs32(mz), st, splits.data());
     };
     int rc = ACSC_OK;
     if (phases & kPhaseSubspace) {
@@ -2366,8 +2004,7 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         std::vector<chol::Req> cj;
         std::vector<JacJob> jj;
         // the last product of the subspace phase lies in the partials of its plan
-        if (use16)
-            splits = pass::plan_splits(reqs16(false));
+        splits = use16 ? pass::plan_splits(reqs16(false)) : f32::plan_splits(reqs32(false));
         for (auto &m : ms) {
             A.push_back(m.pw.Z);
             rows.push_back(m.D.n);
@@ -2395,18 +2032,7 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         og.push_back(orth::GemmReq{m.pw.Y, KP, m.D.m, KP, m.pw.Bu, RP, RP, m.in->U, nullptr, r, r});
         og.push_back(orth::GemmReq{m.pw.Z, KP, m.D.n, KP, m.pw.Bv, RP, RP, m.in->V, nullptr, r, r});
     }
-    bool fast = true;
-    for (const auto &q : og)
-        fast = fast && orth::gemm_supported(q);
-    if (fast)
-        return orth::gemm("sc_basis", og, st);
-    std::vector<GemmReq<float, float>> g;
-    for (auto &m : ms) {
-        g.push_back(GemmReq<float, float>{m.pw.Y, KP, m.pw.Bu, RP, m.in->U, r, m.D.m, KP, r, r, nullptr, nullptr, 0});
-        g.push_back(GemmReq<float, float>{m.pw.Z, KP, m.pw.Bv, RP, m.in->V, r, m.D.n, KP, r, r, nullptr, nullptr, 0});
-    }
-    tall_gemm<float, false, float>("sc_basis", g, st);
-    return ACSC_OK;
+    return orth::gemm("sc_basis", og, st);
 }
 
 // Squared global norm of the call's G_proj and the clip coefficient (see
@@ -2459,31 +2085,21 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
         if (rc)
             return rc;
     } else {
-        std::vector<GemmReq<float, float>> q;
+        std::vector<f32::PassReq> q;
         for (auto &m : ms)
-            q.push_back(GemmReq<float, float>{static_cast<const float *>(m.in->G), m.D.n, m.in->V, r, m.cw.Tm, RP,
-                                              m.D.m, m.D.n, r, RP, m.cw.part, nullptr, 0});
-        tall_gemm<float, false, float>("sc_gv", q, st);
+            q.push_back(f32::PassReq{static_cast<const float *>(static_cast<const void *>(m.in->G)), m.D.n, m.in->V, r,
+                                     m.cw.Tm, RP, m.D.m, m.D.n, r, RP, m.cw.part, split_count(m.D.m, m.D.n)});
+        if (int rc = f32::pass("sc_gv", false, q, st))
+            return rc;
     }
     // X = U^T T   [r, RP]
     {
         std::vector<orth::InnerReq> iq;
-        bool fast = true;
-        for (auto &m : ms) {
+        for (auto &m : ms)
             iq.push_back(orth::InnerReq{m.in->U, r, m.cw.Tm, RP, m.D.m, r, RP, m.cw.X, RP, m.cw.xpart,
                                         split_count(m.D.r, m.D.m)});
-            fast = fast && orth::inner_supported(iq.back());
-        }
-        if (fast) {
-            if (int rc = orth::inner("sc_utt", iq, st))
-                return rc;
-        } else {
-            std::vector<GemmReq<float, float>> q;
-            for (auto &m : ms)
-                q.push_back(GemmReq<float, float>{m.in->U, r, m.cw.Tm, RP, m.cw.X, RP, r, m.D.m, RP, RP, m.cw.xpart,
-                                                  nullptr, 0});
-            tall_gemm<float, true, float>("sc_utt", q, st);
-        }
+        if (int rc = orth::inner("sc_utt", iq, st))
+            return rc;
     }
     {
         std::vector<FilterJob> f;
@@ -2493,29 +2109,18 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
     }
     // P = U X_f  [m, RP] in the compute type; V in the compute type [n, RP]
     {
-        std::vector<GemmReq<float, GT>> q;
         std::vector<PadJob<GT>> pj;
+        std::vector<orth::GemmReq> og;
         int64_t tot = 1;
         for (auto &m : ms) {
-            q.push_back(GemmReq<float, GT>{m.in->U, r, m.cw.Xf, RP, static_cast<GT *>(m.cw.Pc), RP, m.D.m, r, RP, RP,
-                                           nullptr, nullptr, 0});
             pj.push_back(PadJob<GT>{m.in->V, m.D.n, static_cast<GT *>(m.cw.Vc)});
             tot = std::max<int64_t>(tot, static_cast<int64_t>(m.D.n) * RP);
-        }
-        std::vector<orth::GemmReq> og;
-        bool fast = true;
-        for (auto &m : ms) {
             og.push_back(orth::GemmReq{m.in->U, r, m.D.m, r, m.cw.Xf, RP, RP,
                                        b16 ? nullptr : static_cast<float *>(m.cw.Pc),
                                        b16 ? static_cast<uint16_t *>(m.cw.Pc) : nullptr, RP, RP});
-            fast = fast && orth::gemm_supported(og.back());
         }
-        if (fast) {
-            if (int rc = orth::gemm("sc_ux", og, st))
-                return rc;
-        } else {
-            tall_gemm<float, false, GT>("sc_ux", q, st);
-        }
+        if (int rc = orth::gemm("sc_ux", og, st))
+            return rc;
         if (!b16)   // the bf16 copy was made with the transposed one
             launch_jobs("sc_vconvert", pad_convert_kernel<GT>, pj, dim3(grid1d(tot)), dim3(256), 0, st, r, RP);
     }
@@ -2524,16 +2129,6 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
     const blend::AdamArgs ad = adam ? adam->args : blend::AdamArgs{};
     const char *btag = adam ? "sc_blend_adamw" : "sc_blend";
     {
-        std::vector<BlendJob<GT>> bj;
-        int gx = 1, gy = 1;
-        for (auto &m : ms) {
-            bj.push_back(BlendJob<GT>{static_cast<const GT *>(m.in->G), static_cast<GT *>(m.in->G_proj), m.D.m, m.D.n,
-                                      static_cast<const GT *>(m.cw.Pc), static_cast<const GT *>(m.cw.Vc),
-                                      m.ad ? m.ad->W : nullptr, m.ad ? m.ad->m1 : nullptr,
-                                      m.ad ? m.ad->m2 : nullptr, nullptr});
-            gx = std::max<int>(gx, static_cast<int>(cdiv(m.D.n, 64)));
-            gy = std::max<int>(gy, static_cast<int>(cdiv(m.D.m, 64)));
-        }
         if constexpr (sizeof(GT) == 2) {
             if (blend::supported(RP)) {
                 std::vector<blend::Req> q;
@@ -2545,6 +2140,12 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
                 return blend::run(btag, q, RP, alpha, st, adam ? &ad : nullptr);
             }
             // 128 x 128 tiles, XCD-aware order (see blend16_kernel)
+            std::vector<BlendJob<GT>> bj;
+            for (auto &m : ms)
+                bj.push_back(BlendJob<GT>{static_cast<const GT *>(m.in->G), static_cast<GT *>(m.in->G_proj), m.D.m, m.D.n,
+                                          static_cast<const GT *>(m.cw.Pc), static_cast<const GT *>(m.cw.Vc),
+                                          m.ad ? m.ad->W : nullptr, m.ad ? m.ad->m1 : nullptr,
+                                          m.ad ? m.ad->m2 : nullptr, nullptr});
             int tiles = 1, cbm = 1;
             bool vec = true;
             for (auto &m : ms) {
@@ -2565,12 +2166,14 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
                     launch_jobs(btag, blend16_kernel<false, false>, bj, dim3(tiles), dim3(256), 0, st, RP, alpha, cbm, ad);
             }
         } else {
-            const size_t pitch = RP + 1;
-            const size_t blds = 2 * 64 * pitch * sizeof(GT);
-            if (adam)
-                launch_jobs(btag, blend_kernel<GT, blend::kAdam>, bj, dim3(gx, gy), dim3(256), blds, st, RP, alpha, ad);
-            else
-                launch_jobs(btag, blend_kernel<GT, blend::kPlain>, bj, dim3(gx, gy), dim3(256), blds, st, RP, alpha, ad);
+            std::vector<f32::BlendReq> q;
+            for (auto &m : ms)
+                q.push_back(f32::BlendReq{static_cast<const float *>(static_cast<const void *>(m.in->G)),
+                                          static_cast<float *>(m.in->G_proj), m.D.m, m.D.n,
+                                          static_cast<const float *>(m.cw.Pc), static_cast<const float *>(m.cw.Vc),
+                                          m.ad ? m.ad->W : nullptr, m.ad ? m.ad->m1 : nullptr,
+                                          m.ad ? m.ad->m2 : nullptr, nullptr});
+            return f32::blend(btag, q, RP, alpha, st, adam ? &ad : nullptr, false);
         }
     }
     return ACSC_OK;
@@ -2728,7 +2331,7 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
     } else {
         std::vector<PadJob<float>> pj;
         std::vector<Ema32Job<float>> ej;
-        std::vector<GemmReq<float, float>> q;
+        std::vector<f32::PassReq> q;
         int64_t tp = 1, te = 1;
         for (auto &x : it) {
             pj.push_back(PadJob<float>{x.in->Q, x.in->n, x.w.pw.Z});
@@ -2736,12 +2339,13 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
             const int64_t c = static_cast<int64_t>(x.in->m) * x.in->n;
             ej.push_back(Ema32Job<float>{x.in->E, static_cast<const float *>(x.in->G), c});
             te = std::max(te, cdiv(c, 4));
-            q.push_back(GemmReq<float, float>{x.in->E, x.in->n, x.w.pw.Z, KP, x.w.pw.Y, KP, x.in->m, x.in->n, r, KP,
-                                              x.w.pw.part, nullptr, 0});
+            q.push_back(f32::PassReq{x.in->E, x.in->n, x.w.pw.Z, KP, x.w.pw.Y, KP, x.in->m, x.in->n, r, KP,
+                                     x.w.pw.part, split_count(x.in->m, x.in->n)});
         }
         launch_jobs("psgd_qconvert", pad_convert_kernel<float>, pj, dim3(grid1d(tp)), dim3(256), 0, st, r, KP);
         launch_jobs("psgd_feedback", ema_kernel<float>, ej, dim3(grid1d(te)), dim3(256), 0, st, 1.0f, 1.0f);
-        tall_gemm<float, false, float>("psgd_pass_mq", q, st);
+        if (int rc = f32::pass("psgd_pass_mq", false, q, st, splits.data()))
+            return rc;
     }
     std::vector<CropJob> cj;
     for (size_t i = 0; i < it.size(); ++i)
@@ -2781,11 +2385,12 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
         if (int rc = pass::run("psgd_pass_mtp", true, q, st, splits.data()))
             return rc;
     } else {
-        std::vector<GemmReq<float, float>> q;
+        std::vector<f32::PassReq> q;
         for (auto &x : it)
-            q.push_back(GemmReq<float, float>{x.in->E, x.in->n, x.w.pw.Y, KP, x.w.pw.Z, KP, x.in->n, x.in->m, r, KP,
-                                              x.w.pw.part, nullptr, 0});
-        tall_gemm<float, true, float>("psgd_pass_mtp", q, st);
+            q.push_back(f32::PassReq{x.in->E, x.in->n, x.w.pw.Y, KP, x.w.pw.Z, KP, x.in->n, x.in->m, r, KP,
+                                     x.w.pw.part, split_count(x.in->n, x.in->m)});
+        if (int rc = f32::pass("psgd_pass_mtp", true, q, st, splits.data()))
+            return rc;
     }
     cj.clear();
     for (size_t i = 0; i < it.size(); ++i)
@@ -2813,24 +2418,18 @@ int psgd_decompress_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStrea
         return blend::run_feedback("psgd_decompress", q, RPd, st);
     }
     std::vector<PadJob<float>> pj;
-    std::vector<BlendJob<float>> bj;
+    std::vector<f32::BlendReq> bj;
     int64_t tp = 1;
-    int gx = 1, gy = 1;
     for (auto &x : it) {
         pj.push_back(PadJob<float>{x.in->P, x.in->m, static_cast<float *>(x.w.Pc)});
         pj.push_back(PadJob<float>{x.in->Q, x.in->n, static_cast<float *>(x.w.Vc)});
         tp = std::max<int64_t>(tp, static_cast<int64_t>(std::max(x.in->m, x.in->n)) * RPd);
-        bj.push_back(BlendJob<float>{nullptr, static_cast<float *>(x.in->out), x.in->m, x.in->n,
-                                     static_cast<const float *>(x.w.Pc), static_cast<const float *>(x.w.Vc), nullptr,
-                                     nullptr, nullptr, x.in->E});
-        gx = std::max<int>(gx, static_cast<int>(cdiv(x.in->n, 64)));
-        gy = std::max<int>(gy, static_cast<int>(cdiv(x.in->m, 64)));
+        bj.push_back(f32::BlendReq{nullptr, static_cast<float *>(x.in->out), x.in->m, x.in->n,
+                                   static_cast<const float *>(x.w.Pc), static_cast<const float *>(x.w.Vc), nullptr,
+                                   nullptr, nullptr, x.in->E});
     }
     launch_jobs("psgd_fconvert", pad_convert_kernel<float>, pj, dim3(grid1d(tp)), dim3(256), 0, st, r, RPd);
-    const size_t blds = 2 * 64 * static_cast<size_t>(RPd + 1) * sizeof(float);
-    launch_jobs("psgd_decompress", blend_kernel<float, blend::kFeedback>, bj, dim3(gx, gy), dim3(256), blds, st, RPd,
-                0.0f, blend::AdamArgs{});
-    return ACSC_OK;
+    return f32::blend("psgd_decompress", bj, RPd, 0.0f, st, nullptr, true);
 }
 
 int check_psgd(const psgd_matrix &a, int i, int r, acsc_dtype dt, int phase)
@@ -2882,11 +2481,6 @@ int psgd_run(int count, const psgd_matrix *mats, acsc_dtype dt, int r, int phase
     const bool use16 = dt == ACSC_BF16;
     if (int rc = chol::prepare(it[0].mat.D.KP))
         return rc;
-    if (!use16) {
-        const size_t blds = 2 * 64 * static_cast<size_t>(it[0].w.RPd + 1) * sizeof(float);
-        if (int rc = allow_lds(blend_kernel<float, blend::kFeedback>, blds))
-            return rc;
-    }
     int rc = ACSC_OK;
     if (phase == 0 || phase == 3)
         rc = psgd_project_phase(it, use16, r, st);
@@ -3068,11 +2662,7 @@ extern "C" int sc_correct_batched(int count, const sc_matrix *mats, acsc_dtype d
     }
     if (all.empty())
         return ACSC_OK;
-    const size_t es = dtype_size(dt);
-    const size_t blds = 2 * 64 * (all[0].D.RP + (dt == ACSC_BF16 ? 8 : 1)) * es;
-    int rc = dt == ACSC_BF16 ? allow_lds(blend_kernel<uint16_t, blend::kPlain>, blds) : allow_lds(blend_kernel<float, blend::kPlain>, blds);
-    if (rc)
-        return rc;
+    int rc = ACSC_OK;
     if (dt == ACSC_BF16)
         rc = correct_group<uint16_t>(all, r, alpha, stream);
     else
@@ -3133,11 +2723,7 @@ extern "C" int sc_correct_adamw_batched(int count, const sc_matrix *mats, const 
     }
     if (all.empty())
         return ACSC_OK;
-    const size_t es = dtype_size(dt);
-    const size_t blds = 2 * 64 * (all[0].D.RP + (dt == ACSC_BF16 ? 8 : 1)) * es;
-    int rc = dt == ACSC_BF16 ? allow_lds(blend_kernel<uint16_t, blend::kAdam>, blds) : allow_lds(blend_kernel<float, blend::kAdam>, blds);
-    if (rc)
-        return rc;
+    int rc = ACSC_OK;
     // bias corrections and the step size in double on the host, then fp32
     const double t = static_cast<double>(hp->step);
     const double bc1 = 1.0 - std::pow(static_cast<double>(hp->beta1), t);

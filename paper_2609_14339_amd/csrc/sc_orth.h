@@ -40,11 +40,9 @@ struct GemmReq {
     int nwrite;
 };
 
-// Whether gemm() takes these operands: 16-byte aligned A and B whose row
-// strides, K and N are multiples of 4, K and N at most SC_KMAX.
-bool gemm_supported(const GemmReq &q);
-
-// Enqueue C = A B for every request on `st`.
+// Enqueue C = A B for every request on `st`: B 16-byte aligned, its row stride
+// and N multiples of 4, K and N at most SC_KMAX; A element-aligned with any
+// row stride.
 int gemm(const char *tag, const std::vector<GemmReq> &reqs, hipStream_t st);
 
 // C = A^T B over the rows of two tall blocks, A [rows, NA], B [rows, NB]
@@ -63,9 +61,7 @@ struct InnerReq {
     int part_blocks;
 };
 
-// Whether inner() takes these operands (alignment as for gemm(), and room in
-// `part` for at least one block of round_up(max(NA, NB), 32)^2 floats).
-bool inner_supported(const InnerReq &q);
+// Alignment as for gemm(), NB a multiple of 4.
 int inner(const char *tag, const std::vector<InnerReq> &reqs, hipStream_t st);
 
 }  // namespace orth

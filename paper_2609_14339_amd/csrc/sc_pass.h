@@ -44,6 +44,18 @@ inline int64_t tiled_elems(int64_t R, int64_t C) { return tiles_per_row(R) * til
 // caller sizes `part` for it.
 int max_splits(int64_t M, int64_t K);
 
+// Partials of a product that was cut along k: partial p at part + p *
+// split_stride, row stride NP (a multiple of 4); add_partials stores their
+// sum, in order, to C.
+struct Partials {
+    const float *part;
+    int64_t split_stride;
+    float *C;
+    int64_t ldc;
+    int M, NP, splits;
+};
+void add_partials(const std::vector<Partials> &red, hipStream_t st);
+
 // The k pieces that run() cuts each request into (a function of the shapes).
 std::vector<int> plan_splits(const std::vector<Req> &reqs);
 

@@ -133,6 +133,33 @@ def test_passes_cut_into_uneven_pieces(pk, shapes, r):
         assert osp.projector_distance(_np(U), U0) < 2e-2 and osp.projector_distance(_np(V), V0) < 2e-2
 
 
+@pytest.mark.parametrize("m,n,r", [(17, 40, 5), (4100, 1037, 13), (16400, 515, 33), (16391, 1030, 150), (130, 9001, 100),
+                                   (16384, 2048, 64), (64, 33, 32)])
+def test_fp32_products_at_the_edges_of_their_tiles(pk, m, n, r):
+    """The fp32 products take 16-row workgroups or, where they fill the GPU,
+    64-row ones (32 beyond 144 columns), cut k among waves and workgroups, and
+    mask tails of k, rows and columns; rows of odd widths are not 16-byte
+    aligned.  Correction and one PowerSGD step against 64 bits."""
+    U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=m + n + r)
+    G = (((U * 0.5) @ V.T) + 0.02 * workloads.gaussian((m, n), seed=4).double()).float()
+    d = osp.filter_weights(s.numpy(), 0.7)
+    ref = osp.correct(_np(G), U.numpy(), d, V.numpy(), 0.3)
+    out = torch.full((m, n), float("nan"), device="cuda")
+    pk.sc_correct(G.cuda(), U.float().cuda(), torch.tensor(d, dtype=torch.float32).cuda(), V.float().cuda(), 0.3,
+                  out=out)
+    torch.cuda.synchronize()
+    assert osp.rel_fro(_np(out), ref) <= 2e-6
+    Q0 = workloads.gaussian((n, r), seed=8)
+    it = dict(G=G.cuda(), E=torch.zeros(m, n, device="cuda"), P=torch.empty(m, r, device="cuda"), Q=Q0.cuda(),
+              out=torch.full((m, n), float("nan"), device="cuda"), ws=pk.psgd_workspace(m, n, r, torch.float32))
+    pk.psgd_step([it], r, torch.float32)
+    torch.cuda.synchronize()
+    P, R = np.linalg.qr(_np(G) @ _np(Q0))
+    P *= np.sign(np.diag(R))
+    Q = _np(G).T @ P
+    assert osp.rel_fro(_np(it["Q"]), Q) <= 1e-4 and osp.rel_fro(_np(it["out"]), P @ Q.T) <= 1e-4
+
+
 def test_correct_in_place_and_alpha_one(pk):
     m, n, r = 512, 384, 16
     U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=1)
