@@ -157,8 +157,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:
+        # the current stream's handle without the Stream object around it (0.2 us against 2.8 a call)
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return C.c_void_p(stream.cuda_stream)
 
 
 def _need_cuda(*ts):

@@ -10,7 +10,8 @@ dL/dh = scale * (dL/dh~ ⊙ m) and masked positions get exactly zero.
 
 BoundarySend / BoundaryRecv are the two halves, for a sender and a receiver
 on different pipeline stages (the packed values are what crosses the link in
-both directions); masked_boundary chains them on one device.  The scale is
+both directions); masked_boundary is the two of them on one device, as one
+autograd node.  The scale is
 applied wherever a payload is unpacked, in both directions (the receiver of
 each direction absorbs it): the backward payload is the unscaled packed
 gradient, and the pair together gives exactly dL/dh = scale * (dL/dh~ ⊙ m).
@@ -22,7 +23,7 @@ from __future__ import annotations
 
 import torch
 
-from . import ac_keep_count, ac_mask_pack, ac_unpack_scatter, make_key
+from . import ac_keep_count, ac_mask_pack, ac_mask_pack_batched, ac_unpack_scatter, make_key
 
 
 def boundary_key(seed: int, layer: int, step: int, microbatch: int, h: torch.Tensor):
@@ -72,6 +73,33 @@ class BoundaryRecv(torch.autograd.Function):
         return g_vals, None, None, None, None
 
 
+class _MaskedBoundary(torch.autograd.Function):
+    """BoundarySend and BoundaryRecv on one device as one node: the same bits
+    from the same kernels, with one pass through the autograd engine each way
+    (its host work is what a small boundary waits for: 44 us of a forward call
+    and 125 us of a backward call were host time), no zero gradient made for
+    the index list, and the gradient packed at the kept positions instead of
+    from a second evaluation of the mask."""
+
+    @staticmethod
+    def forward(ctx, h: torch.Tensor, K: int, key, scale: float):
+        B, S, H = h.shape
+        vals, idx = ac_mask_pack(h.reshape(B * S, H), K, key)
+        y = ac_unpack_scatter(vals, H, key, scale, idx=idx)
+        ctx.key, ctx.scale, ctx.shape = key, scale, (B, S, H)
+        ctx.save_for_backward(idx)
+        return y.view(B, S, H)
+
+    @staticmethod
+    def backward(ctx, g_y: torch.Tensor):
+        (idx,) = ctx.saved_tensors
+        B, S, H = ctx.shape
+        rows, K = idx.shape
+        g_vals = ac_mask_pack_batched(g_y.contiguous().view(1, rows, H), K, ctx.key, idx_in=idx.view(1, rows, K))
+        g = ac_unpack_scatter(g_vals.view(rows, K), H, ctx.key, ctx.scale, idx=idx)
+        return g.view(B, S, H), None, None, None
+
+
 def masked_boundary(h: torch.Tensor, keep: float, key, scale=None) -> torch.Tensor:
     """scale * (h ⊙ m) with K = round(keep * H) kept per token; gradients
     flow through the same mask.  scale defaults to H / K (unbiased for a
@@ -80,5 +108,4 @@ def masked_boundary(h: torch.Tensor, keep: float, key, scale=None) -> torch.Tens
     H = h.shape[-1]
     K = ac_keep_count(H, keep)
     s = H / K if scale is None else float(scale)
-    vals, idx = BoundarySend.apply(h, K, key, s)
-    return BoundaryRecv.apply(vals, idx, tuple(h.shape), key, s)
+    return _MaskedBoundary.apply(h, K, key, s)

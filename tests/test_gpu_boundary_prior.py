@@ -76,6 +76,30 @@ def test_boundary_forward_and_backward_bit_exact(pk, dtype, B, S, H, keep):
     assert torch.equal(y2, y) and torch.equal(h2.grad, h.grad)
 
 
+@pytest.mark.parametrize("B,S,H,keep", [(1, 1, 1, 1.0), (3, 7, 65, 0.02), (2, 31, 8192, 0.02), (1, 130, 2047, 0.3)])
+def test_masked_boundary_is_its_two_halves(pk, B, S, H, keep):
+    """One autograd node gives the bits of the chained halves in both
+    directions, for a strided activation and a strided gradient too, on a
+    side stream, and again when the graph is kept."""
+    from paper_2609_14339_amd.autograd import BoundaryRecv, BoundarySend, boundary_key, masked_boundary
+    h0 = workloads.gaussian((S, B, H), seed=H, dtype=torch.bfloat16).cuda().transpose(0, 1)
+    gy = workloads.gaussian((B, H, S), seed=H + 1, dtype=torch.bfloat16).cuda().transpose(1, 2)
+    key = boundary_key(5, 3, 11, 2, h0)
+    K = om.keep_count(H, keep)
+    got, want = (h0.detach().requires_grad_(True) for _ in range(2))
+    y2 = BoundaryRecv.apply(*BoundarySend.apply(want, K, key, H / K), (B, S, H), key, H / K)
+    y2.backward(gy)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        y = masked_boundary(got, keep, key)
+        for _ in range(2):
+            (g,) = torch.autograd.grad(y, got, gy, retain_graph=True)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
+    assert torch.equal(g.contiguous().view(torch.int16), want.grad.contiguous().view(torch.int16))
+
+
 def test_boundary_inside_a_two_layer_model(pk):
     """x -> Linear -> masked boundary -> Linear -> loss: the weight gradients
     match a PyTorch fp32 CPU reference that applies the oracle's mask."""
