@@ -50,15 +50,19 @@ struct Batch {
 // the same map takes a slot back to its chunk).  Measured with the bank
 // conflict counter on MI355X: 256-byte rows need all four chunk bits mixed
 // with the row's low bits for the 16 rows a fragment read touches to spread
-// over every bank; other row widths mix the low three bits with
-// (r >> 1) ^ r.  Either way a fragment read runs without bank conflicts.
+// over every bank; other multiples of 128 mix the low three bits with
+// (r >> 1) ^ r; rows of an odd number of 64 bytes start at four places, and
+// the rows that share one are told apart by two bits.  Either way a fragment
+// read runs without bank conflicts.
 template <int RB>
 __device__ __forceinline__ int slot_of(int c, int r)
 {
     if constexpr (RB == 256)
         return c ^ (r & 15);
-    else
+    else if constexpr (RB % 128 == 0)
         return (c & ~7) | ((c & 7) ^ (((r >> 1) ^ r) & 7));
+    else
+        return c ^ ((r >> 2) & 3);
 }
 
 // global_load_lds_dwordx4 takes its wave-uniform LDS address in M0.  The asm
@@ -113,7 +117,7 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
     constexpr int RB = RP * 2;                  // bytes per P / V row
     constexpr int SLICE = kT * RB;              // bytes of one 128-row slice
     constexpr int NI = 2 * SLICE / 1024;        // DMA instructions for P and V
-    static_assert(NI % 4 == 0 && RB % 128 == 0, "slice layout");
+    static_assert(NI % 4 == 0 && RB % 64 == 0, "slice layout");
     constexpr int LDS = (2 * SLICE > kT * kStPitch * 4) ? 2 * SLICE : kT * kStPitch * 4;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
 
@@ -190,11 +194,16 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
             uint4 v = make_uint4(0u, 0u, 0u, 0u);
             if (gi < m) {
                 const uint16_t *src = J.G + static_cast<int64_t>(gi) * n + gj;
-                uint16_t e8[8];
+                if (gj + 8 <= n) {
+                    const Bf8Any x = *reinterpret_cast<const Bf8Any *>(src);
+                    v = make_uint4(x.w[0], x.w[1], x.w[2], x.w[3]);
+                } else {
+                    uint16_t e8[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    e8[e] = gj + e < n ? src[e] : uint16_t(0);
-                __builtin_memcpy(&v, e8, sizeof(v));
+                    for (int e = 0; e < 8; ++e)
+                        e8[e] = gj + e < n ? src[e] : uint16_t(0);
+                    __builtin_memcpy(&v, e8, sizeof(v));
+                }
             }
             g[u] = v;
         }
@@ -289,6 +298,18 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
                 __builtin_nontemporal_store(ov, reinterpret_cast<nu4 *>(J.out + o));
                 __builtin_nontemporal_store(e0, reinterpret_cast<nf4 *>(J.E + o));
                 __builtin_nontemporal_store(e1, reinterpret_cast<nf4 *>(J.E + o) + 1);
+            } else if (gj + 8 <= n) {
+                F4Any e0 = *reinterpret_cast<const F4Any *>(J.E + o), e1 = *reinterpret_cast<const F4Any *>(J.E + o + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    e0.v[e] -= of[e];
+                    e1.v[e] -= of[4 + e];
+                }
+                Bf8Any ov;
+                __builtin_memcpy(&ov, ob, sizeof(ov));
+                *reinterpret_cast<Bf8Any *>(J.out + o) = ov;
+                *reinterpret_cast<F4Any *>(J.E + o) = e0;
+                *reinterpret_cast<F4Any *>(J.E + o + 4) = e1;
             } else {
                 for (int e = 0; e < 8 && gj + e < n; ++e) {
                     J.out[o + e] = ob[e];
@@ -343,6 +364,19 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
                     __builtin_nontemporal_store(mv[h], reinterpret_cast<nf4 *>(J.m1 + o) + h);
                     __builtin_nontemporal_store(vv[h], reinterpret_cast<nf4 *>(J.m2 + o) + h);
                 }
+            } else if (gj + 8 <= n) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    F4Any wv = *reinterpret_cast<const F4Any *>(J.W + o + 4 * h);
+                    F4Any mv = *reinterpret_cast<const F4Any *>(J.m1 + o + 4 * h);
+                    F4Any vv = *reinterpret_cast<const F4Any *>(J.m2 + o + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        adamw_elem(gp[4 * h + e], wv.v[e], mv.v[e], vv.v[e], ad);
+                    *reinterpret_cast<F4Any *>(J.W + o + 4 * h) = wv;
+                    *reinterpret_cast<F4Any *>(J.m1 + o + 4 * h) = mv;
+                    *reinterpret_cast<F4Any *>(J.m2 + o + 4 * h) = vv;
+                }
             } else {
                 for (int e = 0; e < 8 && gj + e < n; ++e) {
                     float wv = J.W[o + e], mv = J.m1[o + e], vv = J.m2[o + e];
@@ -393,6 +427,8 @@ __global__ __launch_bounds__(256) void blend_kernel(const Batch jb, float alpha,
         uint16_t *dst = J.out + static_cast<int64_t>(gi) * n + gj;
         if (VEC && gj + 8 <= n) {
             __builtin_nontemporal_store(o, reinterpret_cast<nu4 *>(dst));
+        } else if (gj + 8 <= n) {
+            *reinterpret_cast<Bf8Any *>(dst) = Bf8Any{{o.x, o.y, o.z, o.w}};
         } else {
             uint16_t e8[8];   // (a copy, not a pointer cast: read as another type, the words are not the compiler's to keep)
             __builtin_memcpy(e8, &o, sizeof(e8));
@@ -430,8 +466,11 @@ void launch_mode(const char *tag, int RP, const std::vector<Job> &jobs, int tile
                  hipStream_t st)
 {
     switch (RP) {
+    case 32: launch_rp<32, MODE>(tag, jobs, tiles, alpha, ad, st); break;
     case 64: launch_rp<64, MODE>(tag, jobs, tiles, alpha, ad, st); break;
+    case 96: launch_rp<96, MODE>(tag, jobs, tiles, alpha, ad, st); break;
     case 128: launch_rp<128, MODE>(tag, jobs, tiles, alpha, ad, st); break;
+    case 160: launch_rp<160, MODE>(tag, jobs, tiles, alpha, ad, st); break;
     default: launch_rp<192, MODE>(tag, jobs, tiles, alpha, ad, st); break;
     }
 }
@@ -439,8 +478,8 @@ void launch_mode(const char *tag, int RP, const std::vector<Job> &jobs, int tile
 int launch_all(const char *tag, const std::vector<Req> &reqs, int RP, float alpha, hipStream_t st,
                const AdamArgs *adam, bool feedback)
 {
-    if (!supported(RP))
-        return set_error(ACSC_EINVAL, "blend: padded rank %d not handled by the streamed-tile kernel", RP);
+    if (RP < 32 || RP % 32 != 0 || RP > SC_KMAX)
+        return set_error(ACSC_EINVAL, "blend: padded rank %d (a multiple of 32 up to %d)", RP, SC_KMAX);
     std::vector<Job> jobs;
     int tiles = 1;
     auto a16 = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
@@ -463,8 +502,6 @@ int launch_all(const char *tag, const std::vector<Req> &reqs, int RP, float alph
 }
 
 }  // namespace
-
-bool supported(int RP) { return RP == 64 || RP == 128 || RP == 192; }
 
 int run(const char *tag, const std::vector<Req> &reqs, int RP, float alpha, hipStream_t st, const AdamArgs *adam)
 {

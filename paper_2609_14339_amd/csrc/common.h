@@ -90,6 +90,15 @@ __device__ __forceinline__ float blend_step(float g, float p, float alpha, float
     return __builtin_fmaf(alpha, g, oma * p);
 }
 
+// 16-byte accesses at any element's alignment (the hardware takes them; only
+// the declared type says so): eight bf16, four floats.
+struct __attribute__((packed, aligned(2))) Bf8Any {
+    uint32_t w[4];
+};
+struct __attribute__((packed, aligned(4))) F4Any {
+    float v[4];
+};
+
 // Sum, in order, of `splits` >= 1 partials `ss` floats apart (16-byte aligned).
 // The loads of four partials are issued before the first is added: one at a
 // time, each addition waits a memory latency (the Gram kernel of six 1B-class

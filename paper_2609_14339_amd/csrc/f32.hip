@@ -24,10 +24,7 @@ namespace f32 {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-// a 16-byte access that needs element alignment only
-struct __attribute__((packed, aligned(4))) F4 {
-    float v[4];
-};
+using F4 = F4Any;
 
 constexpr int kMaxJobs = 16;
 

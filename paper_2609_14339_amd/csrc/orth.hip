@@ -9,6 +9,7 @@
 // so that each of its rows leaves as 16-byte stores.
 #include "common.h"
 #include "sc_orth.h"
+#include "sc_status.h"
 
 #include <algorithm>
 
@@ -21,16 +22,13 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 // Four floats of a row of which `avail` (any number) are left; the rest read
 // as zero.  The row needs element alignment only: priors of a rank that is no
 // multiple of 4 have such rows.
-struct __attribute__((packed, aligned(4))) F4 {
-    float v[4];
-};
 template <bool VEC>   // 16-byte aligned rows, `avail` a multiple of 4
 __device__ __forceinline__ float4 load4(const float *p, int avail)
 {
     if constexpr (VEC)
         return avail > 0 ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
     if (avail >= 4) {
-        const F4 x = *reinterpret_cast<const F4 *>(p);
+        const F4Any x = *reinterpret_cast<const F4Any *>(p);
         return make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
     }
     return make_float4(avail > 0 ? p[0] : 0.f, avail > 1 ? p[1] : 0.f, avail > 2 ? p[2] : 0.f, 0.f);
@@ -55,6 +53,7 @@ struct Job {
     int nwrite;
     uint16_t *Ct16;
     int64_t ldq;
+    int *stamp;
 };
 struct Batch {
     int count;
@@ -85,6 +84,8 @@ __global__ __launch_bounds__(256) void tall_small_kernel(const Batch jb)
     const int row0 = blockIdx.x * kRows;
     if (row0 >= rows)
         return;
+    if (J.stamp && blockIdx.x == 0 && threadIdx.x == 0)
+        stamp_subspace(J.stamp);
     const float *A = J.A;
     const float *B = J.B;
     const int64_t lda = J.lda, ldb = J.ldb;
@@ -278,7 +279,11 @@ int launch_all(const char *tag, const std::vector<Job> &jobs, hipStream_t st)
 // C = A^T B over row ranges: workgroup b of a job sums rows
 // [b rpb, (b + 1) rpb) into its partial.  Rows arrive in 32-row chunks staged
 // in LDS (A chunk, then B chunk, rows of NT x 32 floats); output tile
-// (ti, tj) of 32 x 32 belongs to wave (ti NT + tj) % 4.
+// (ti, tj) of 32 x 32 belongs to wave (ti NT + tj) % 4.  The chunks of a range
+// are a serial chain, and the partials' room limits how short ranges get: a
+// batch whose ranges do not fill the GPU gives each tile row ti a workgroup
+// of its own (CUT; blockIdx.y), which stages 32 columns of A only.  X = U^T T
+// of a 4096 x 4096 matrix at rank 100: 36 us uncut, 14 us cut.
 struct InnerJob {
     const float *A;
     int64_t lda;
@@ -292,16 +297,18 @@ struct InnerBatch {
     InnerJob j[kMaxJobs];
 };
 
-template <int NT, bool VEC>
+template <int NT, bool VEC, bool CUT>
 __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
 {
     constexpr int W = NT * 32;                 // staged row width (floats)
     constexpr int P = W + 4;                   // LDS row pitch (16-byte aligned)
-    constexpr int TILES = NT * NT;
+    constexpr int WA = CUT ? 32 : W;           // columns of A staged
+    constexpr int TILES = CUT ? NT : NT * NT;
     constexpr int TPW = (TILES + 3) / 4;
     constexpr int CV = 32 * (W / 4);           // float4 of one operand chunk
     constexpr int PF = (CV + 255) / 256;       // float4 per thread and operand
-    __shared__ __attribute__((aligned(16))) float As[32 * P], Bs[32 * P];
+    __shared__ __attribute__((aligned(16))) float As[32 * (WA + 4)], Bs[32 * P];
+    const int ti0 = CUT ? static_cast<int>(blockIdx.y) : 0;
     const InnerJob &J = jb.j[blockIdx.z];
     if (static_cast<int>(blockIdx.x) >= J.blocks)
         return;
@@ -318,34 +325,41 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
         for (int e = 0; e < 16; ++e)
             acc[u][e] = 0.f;
 
-    float4 pa[PF], pb[PF];
+    constexpr int PA = WA + 4;
+    constexpr int AV = 32 * (WA / 4), PFA = (AV + 255) / 256;
+    float4 pa[PFA], pb[PF];
     auto load = [&](int rb) {
+#pragma unroll
+        for (int u = 0; u < PFA; ++u) {
+            const int idx = tid + 256 * u;
+            const int gr = rb + idx / (WA / 4), c = 32 * ti0 + (idx % (WA / 4)) * 4;
+            pa[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (idx < AV && gr < r1)
+                pa[u] = load4<VEC>(J.A + static_cast<int64_t>(gr) * J.lda + c, NA - c);
+        }
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int idx = tid + 256 * u;
-            const int rr = idx / (W / 4), c = (idx % (W / 4)) * 4;
-            const int gr = rb + rr;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-            if (idx < CV && gr < r1) {
-                a = load4<VEC>(J.A + static_cast<int64_t>(gr) * J.lda + c, NA - c);
-                if (c < NB)
-                    b = *reinterpret_cast<const float4 *>(J.B + static_cast<int64_t>(gr) * J.ldb + c);
-            }
-            pa[u] = a;
-            pb[u] = b;
+            const int gr = rb + idx / (W / 4), c = (idx % (W / 4)) * 4;
+            pb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (idx < CV && gr < r1 && c < NB)
+                pb[u] = *reinterpret_cast<const float4 *>(J.B + static_cast<int64_t>(gr) * J.ldb + c);
         }
     };
     load(r0);
     for (int rb = r0; rb < r1; rb += 32) {
         __syncthreads();
 #pragma unroll
+        for (int u = 0; u < PFA; ++u) {
+            const int idx = tid + 256 * u;
+            if (idx < AV)
+                *reinterpret_cast<float4 *>(&As[(idx / (WA / 4)) * PA + (idx % (WA / 4)) * 4]) = pa[u];
+        }
+#pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int idx = tid + 256 * u;
-            if (idx < CV) {
-                const int o = (idx / (W / 4)) * P + (idx % (W / 4)) * 4;
-                *reinterpret_cast<float4 *>(&As[o]) = pa[u];
-                *reinterpret_cast<float4 *>(&Bs[o]) = pb[u];
-            }
+            if (idx < CV)
+                *reinterpret_cast<float4 *>(&Bs[(idx / (W / 4)) * P + (idx % (W / 4)) * 4]) = pb[u];
         }
         __syncthreads();
         if (rb + 32 < r1)
@@ -358,8 +372,8 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
             for (int u = 0; u < TPW; ++u) {
                 const int t = wave + 4 * u;
                 if (t < TILES) {
-                    const int ti = t / NT, tj = t % NT;
-                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(As[row * P + 32 * ti + (lane & 31)],
+                    const int ti = CUT ? 0 : t / NT, tj = CUT ? t : t % NT;
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(As[row * PA + 32 * ti + (lane & 31)],
                                                                   Bs[row * P + 32 * tj + (lane & 31)], acc[u], 0, 0, 0);
                 }
             }
@@ -371,7 +385,7 @@ __global__ __launch_bounds__(256) void tall_inner_kernel(const InnerBatch jb)
     for (int u = 0; u < TPW; ++u) {
         const int t = wave + 4 * u;
         if (t < TILES) {
-            const int ti = t / NT, tj = t % NT;
+            const int ti = CUT ? ti0 : t / NT, tj = CUT ? t : t % NT;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int i = 32 * ti + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3), j = 32 * tj + (lane & 31);
@@ -387,20 +401,26 @@ struct InnerRedJob {
     int blocks, NA, NB;
     float *C;
     int64_t ldc;
+    const float *d;
+    float *Cf;
 };
 struct InnerRedBatch {
     int count;
     InnerRedJob j[kMaxJobs];
 };
 
-// C[i][j] = sum over blocks (fixed order) of part[b][i][j]
+// C[i][j] = sum over blocks (fixed order) of part[b][i][j], and the filtered
+// copy (a launch of its own took 4.7 us)
 __global__ __launch_bounds__(256) void tall_inner_reduce_kernel(const InnerRedBatch jb)
 {
     const InnerRedJob &J = jb.j[blockIdx.z];
     const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= J.NA * J.NB)
-        return;
     const int i = idx / J.NB, j = idx - (idx / J.NB) * J.NB;
+    if (i >= J.NA) {
+        if (J.Cf && i < J.NB)
+            J.Cf[idx] = 0.f;
+        return;
+    }
     const int64_t stride = static_cast<int64_t>(J.NA) * J.NB;
     const float *p = J.part + idx;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -413,7 +433,10 @@ __global__ __launch_bounds__(256) void tall_inner_reduce_kernel(const InnerRedBa
     }
     for (; b < J.blocks; ++b)
         s0 += p[b * stride];
-    J.C[static_cast<int64_t>(i) * J.ldc + j] = (s0 + s1) + (s2 + s3);
+    const float s = (s0 + s1) + (s2 + s3);
+    J.C[static_cast<int64_t>(i) * J.ldc + j] = s;
+    if (J.Cf)
+        J.Cf[idx] = j < J.NA ? J.d[i] * s * J.d[j] : 0.f;
 }
 
 template <int NT>
@@ -429,15 +452,24 @@ void launch_inner(const char *tag, const std::vector<InnerJob> &jobs, const std:
             b.j[i] = jobs[c0 + i];
             rb.j[i] = red[c0 + i];
             gx = std::max(gx, b.j[i].blocks);
-            rx = std::max(rx, (rb.j[i].NA * rb.j[i].NB + 255) / 256);
+            rx = std::max(rx, ((rb.j[i].Cf ? rb.j[i].NB : rb.j[i].NA) * rb.j[i].NB + 255) / 256);
         }
         bool vec = true;
         for (int i = 0; i < b.count; ++i)
             vec = vec && aligned(b.j[i].A, 16) && b.j[i].lda % 4 == 0 && b.j[i].NA % 4 == 0;
-        if (vec)
-            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, true>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+        int64_t total = 0;
+        for (int i = 0; i < b.count; ++i)
+            total += b.j[i].blocks;
+        const bool cut = NT > 1 && total < 256;
+        const dim3 grid(gx, cut ? NT : 1, b.count);
+        if (vec && cut)
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, true, true>), grid, dim3(256), 0, st, b);
+        else if (vec)
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, true, false>), grid, dim3(256), 0, st, b);
+        else if (cut)
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, false, true>), grid, dim3(256), 0, st, b);
         else
-            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, false>), dim3(gx, 1, b.count), dim3(256), 0, st, b);
+            ACSC_LAUNCH(tag, (tall_inner_kernel<NT, false, false>), grid, dim3(256), 0, st, b);
         ACSC_LAUNCH("sc_inner_reduce", tall_inner_reduce_kernel, dim3(rx, 1, rb.count), dim3(256), 0, st, rb);
     }
 }
@@ -457,7 +489,7 @@ int run(const char *tag, const std::vector<Req> &reqs, int KP, hipStream_t st)
         if (!aligned(q.Y, 16) || !aligned(q.T, 16))
             return set_error(ACSC_EINVAL, "orth: Y and T must be 16-byte aligned");
         jobs.push_back(Job{q.Y, KP, q.rows, KP, q.T, KP, KP, 1, q.write32 ? q.Y : nullptr, nullptr, KP, KP,
-                           q.Qt16, q.ldq});
+                           q.Qt16, q.ldq, q.stamp});
     }
     return launch_all(tag, jobs, st);
 }
@@ -486,7 +518,8 @@ int gemm(const char *tag, const std::vector<GemmReq> &reqs, hipStream_t st)
             return set_error(ACSC_EINVAL, "tall product: operands not aligned or sizes out of range");
         if (q.rows < 1)
             continue;
-        jobs.push_back(Job{q.A, q.lda, q.rows, q.K, q.B, q.ldb, q.N, 0, q.C32, q.C16, q.ldc, q.nwrite, nullptr, 0});
+        jobs.push_back(Job{q.A, q.lda, q.rows, q.K, q.B, q.ldb, q.N, 0, q.C32, q.C16, q.ldc, q.nwrite, nullptr, 0,
+                           nullptr});
     }
     return launch_all(tag, jobs, st);
 }
@@ -514,7 +547,7 @@ int inner(const char *tag, const std::vector<InnerReq> &reqs, hipStream_t st)
         rpb = (rpb + 31) / 32 * 32;
         const int blocks = static_cast<int>((q.rows + rpb - 1) / rpb);
         jobs.push_back(InnerJob{q.A, q.lda, q.B, q.ldb, q.rows, q.NA, q.NB, static_cast<int>(rpb), blocks, q.part});
-        red.push_back(InnerRedJob{q.part, blocks, q.NA, q.NB, q.C, q.ldc});
+        red.push_back(InnerRedJob{q.part, blocks, q.NA, q.NB, q.C, q.ldc, q.d, q.Cf});
     }
     if (jobs.empty())
         return ACSC_OK;

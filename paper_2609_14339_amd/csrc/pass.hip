@@ -35,8 +35,6 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 constexpr int kBM = 256;            // output rows per workgroup
 constexpr int kBK = 64;             // depth of one step
 constexpr int kBPitch = kBK + 8;    // bf16 per LDS row of the thin factor (144 B, 16-B aligned)
-constexpr int kTPitch = 66;         // bf16 per k-row of a wave's A^T tile (33 dwords: conflict-free reads)
-constexpr int kMaxNT = SC_KMAX / 16;
 constexpr int kMaxJobs = 16;
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -49,7 +47,7 @@ struct Job {
     int64_t ldbt;
     float *C;
     int64_t ldc, split_stride;
-    int M, K, kchunk, splits, nblocks, avec;
+    int M, K, kchunk, splits, nblocks;
 };
 
 struct Batch {
@@ -97,27 +95,24 @@ __device__ __forceinline__ bf16x8 as_frag(const uint4 &v)
     return f;
 }
 
-// VEC: A rows start 16-byte aligned and the row stride is a multiple of 8,
-// so every 16-byte chunk that starts inside a row lies inside its padded
-// extent.  Loads then need no guards: rows past the end are clamped to the
-// last row (they only feed outputs that are never stored, or meet zero rows
-// of the thin factor) and k is masked when a tail step is staged in LDS.
-// !VEC: element loads with full guards (unaligned operands).
-// NTK column tiles are computed; tiles at or past np / 16 read zeros and are
-// not stored.
-template <bool TRANS, int NTK, bool VEC>
+// Pass over rows that are not 16-byte aligned (a gradient whose width is no
+// multiple of 8): the direct-to-LDS loads below need aligned rows, plain
+// 16-byte loads do not.  Loads never post-process what they fetch (that
+// would wait for the data right after issue): rows past the end are clamped
+// to the last one (they only feed outputs that are never stored), thin-factor
+// addresses into the operand, and what lies past k's end is masked when the
+// registers are stored to LDS.  Only a last step that is not whole takes
+// element loads.
+template <int NT>
 __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
 {
     const Job &J = jb.j[blockIdx.z];
     if (static_cast<int>(blockIdx.x) >= J.nblocks)
         return;
-    constexpr int NT = NTK;
     constexpr int NP = NT * 16;
     constexpr int BCH = NP * (kBK / 8);        // 16-byte chunks of one thin-factor step
     constexpr int BPT = (BCH + 255) / 256;
-    // A step per wave: opA = A: [64 rows][kBPitch] (k contiguous);
-    //                  opA = A^T: [64 k][kTPitch] (rows contiguous)
-    constexpr int AW = TRANS ? kBK * kTPitch : 64 * kBPitch;
+    constexpr int AW = 64 * kBPitch;           // A step per wave: [64 rows][kBPitch]
     __shared__ __attribute__((aligned(16))) uint16_t Bs[2][NP * kBPitch];
     __shared__ __attribute__((aligned(16))) uint16_t As[2][4 * AW];
 
@@ -132,7 +127,6 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
     const int kbeg = split * J.kchunk;
     const int kend = min(J.K, kbeg + J.kchunk);
     const int nsteps = kend > kbeg ? static_cast<int>(cdiv(kend - kbeg, kBK)) : 0;
-    const int bch_live = np * (kBK / 8);
 
     f32x4 acc[4][NT];
 #pragma unroll
@@ -141,18 +135,14 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
         for (int t = 0; t < NT; ++t)
             acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Loads never post-process what they fetch (that would wait for the data
-    // right after issue): addresses are clamped into the operand, and the
-    // masking of a tail step happens when the registers are stored to LDS.
     uint4 rb[BPT];
     auto load_b = [&](int s) {
         const int k0 = kbeg + s * kBK;
 #pragma unroll
         for (int j = 0; j < BPT; ++j) {
             const int q = min(tid + 256 * j, BCH - 1);
-            const int c = min(q >> 3, np - 1);
             const int gk = k0 + (q & 7) * 8;
-            rb[j] = *reinterpret_cast<const uint4 *>(Bt + static_cast<int64_t>(c) * ldbt + (gk < kend ? gk : kbeg));
+            rb[j] = *reinterpret_cast<const uint4 *>(Bt + static_cast<int64_t>(q >> 3) * ldbt + (gk < kend ? gk : kbeg));
         }
     };
     auto store_b = [&](int buf, int s) {
@@ -165,73 +155,33 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
                 uint4 v = rb[j];
                 if (!full)
                     v = keep_first(v, kend - (k0 + (q & 7) * 8));
-                if (q >= bch_live)
-                    v = make_uint4(0u, 0u, 0u, 0u);
                 *reinterpret_cast<uint4 *>(&Bs[buf][(q >> 3) * kBPitch + (q & 7) * 8]) = v;
             }
         }
     };
-    // One step of this wave's A: eight 16-byte chunks per lane, chunk j at
-    // line j * 8 + lane / 8 (a row of A, or a k-row of A^T), 16-byte column
-    // (lane % 8): each 128-byte line is read by eight consecutive lanes.
+    // One step of this wave's A: eight 16-byte chunks per lane, chunk j at row
+    // j * 8 + lane / 8, 16-byte column (lane % 8): each 128-byte line is read
+    // by eight consecutive lanes.
     auto load_a = [&](uint4 (&ra)[8], int s) {
         const int k0 = kbeg + s * kBK;
+        const bool full = k0 + kBK <= kend;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int line = j * 8 + (lane >> 3);
-            const int c8 = (lane & 7) * 8;
-            if (!TRANS) {
-                const int gi = wrow0 + line;
-                const int gk = k0 + c8;
-                if (VEC) {
-                    // rows past M only feed outputs that are never stored
-                    ra[j] = *reinterpret_cast<const uint4 *>(A + static_cast<int64_t>(min(gi, M - 1)) * lda +
-                                                             (gk < kend ? gk : kbeg));
-                } else {
-                    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                    if (gi < M)
-                        v = load8_scalar(A + static_cast<int64_t>(gi) * lda + gk, kend - gk);
-                    ra[j] = v;
-                }
+            const int gk = k0 + (lane & 7) * 8;
+            const uint16_t *src = A + static_cast<int64_t>(min(wrow0 + j * 8 + (lane >> 3), M - 1)) * lda + gk;
+            if (full) {
+                const Bf8Any v = *reinterpret_cast<const Bf8Any *>(src);
+                ra[j] = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
             } else {
-                const int gk = k0 + line;
-                const int gi = wrow0 + c8;
-                if (VEC) {
-                    // k-rows past kend meet zero rows of the thin factor;
-                    // columns past M only feed outputs that are never stored
-                    ra[j] = *reinterpret_cast<const uint4 *>(A + static_cast<int64_t>(min(gk, kend - 1)) * lda +
-                                                             min(gi, (M - 1) & ~7));
-                } else {
-                    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                    if (gk < kend)
-                        v = load8_scalar(A + static_cast<int64_t>(gk) * lda + gi, M - gi);
-                    ra[j] = v;
-                }
+                ra[j] = load8_scalar(src, kend - gk);
             }
         }
     };
-    auto store_a = [&](const uint4 (&ra)[8], int buf, int s) {
-        const int k0 = kbeg + s * kBK;
-        const bool full = k0 + kBK <= kend;
+    auto store_a = [&](const uint4 (&ra)[8], int buf) {
         uint16_t *w = &As[buf][wave * AW];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int line = j * 8 + (lane >> 3);
-            const int c8 = (lane & 7) * 8;
-            if (!TRANS) {
-                uint4 v = ra[j];
-                if (VEC && !full)   // the padding past K may hold anything
-                    v = keep_first(v, kend - (k0 + c8));
-                *reinterpret_cast<uint4 *>(&w[line * kBPitch + c8]) = v;
-            } else {
-                // 33-dword rows: 4-byte stores
-                uint32_t *dst = reinterpret_cast<uint32_t *>(&w[line * kTPitch + c8]);
-                dst[0] = ra[j].x;
-                dst[1] = ra[j].y;
-                dst[2] = ra[j].z;
-                dst[3] = ra[j].w;
-            }
-        }
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<uint4 *>(&w[(j * 8 + (lane >> 3)) * kBPitch + (lane & 7) * 8]) = ra[j];
     };
     auto compute = [&](int buf) {
         const uint16_t *w = &As[buf][wave * AW];
@@ -239,17 +189,9 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
         for (int ks = 0; ks < 2; ++ks) {
             bf16x8 af[4];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (!TRANS) {
-                    af[a] = *reinterpret_cast<const bf16x8 *>(
-                        &w[(a * 16 + (lane & 15)) * kBPitch + ks * 32 + (lane >> 4) * 8]);
-                } else {
-                    const uint16_t *col = &w[(ks * 32 + (lane >> 4) * 8) * kTPitch + a * 16 + (lane & 15)];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        af[a][e] = static_cast<short>(col[e * kTPitch]);
-                }
-            }
+            for (int a = 0; a < 4; ++a)
+                af[a] = *reinterpret_cast<const bf16x8 *>(
+                    &w[(a * 16 + (lane & 15)) * kBPitch + ks * 32 + (lane >> 4) * 8]);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const bf16x8 b = *reinterpret_cast<const bf16x8 *>(
@@ -263,9 +205,8 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
 
     // Pipeline, step s: stage A(s + 1) and B(s + 1) from registers into the
     // other LDS buffers; issue B(s + 2), then A(s + 3) (two steps of A stay in
-    // flight); multiply step s; barrier.  Every step issues the same loads
-    // (step indices past the end are clamped to the last step, which is
-    // still in L2), so the wait counts stay the same around the loop.
+    // flight); multiply step s; barrier.  Step indices past the end are
+    // clamped to the last step, which is still in L2.
     if (nsteps > 0) {
         const int last = nsteps - 1;
         uint4 r0[8], r1[8];
@@ -273,12 +214,12 @@ __global__ __launch_bounds__(256) void pass_kernel(const Batch jb, int np)
         load_a(r0, 0);
         load_a(r1, min(1, last));
         store_b(0, 0);
-        store_a(r0, 0, 0);
+        store_a(r0, 0);
         load_b(min(1, last));
         load_a(r0, min(2, last));
         lds_barrier();
         auto step = [&](int s, uint4 (&nxt)[8]) {
-            store_a(nxt, (s + 1) & 1, s + 1);
+            store_a(nxt, (s + 1) & 1);
             store_b((s + 1) & 1, s + 1);
             load_b(min(s + 2, last));
             load_a(nxt, min(s + 3, last));
@@ -674,18 +615,34 @@ __global__ __launch_bounds__(256) void pass_reduce_kernel(const RedBatch jb)
     }
 }
 
-// Element-load passes (operands that are not 16-byte aligned): one z slice
-// of the grid per job.
-template <bool TRANS>
-void launch_scalar(const char *tag, const std::vector<Job> &jobs, int gx, int np, hipStream_t st)
+// Passes over unaligned rows: one z slice of the grid per job.
+template <int NT>
+void launch_any(const char *tag, const std::vector<Job> &jobs, int gx, int np, hipStream_t st)
 {
     for (size_t c0 = 0; c0 < jobs.size(); c0 += kMaxJobs) {
         Batch b{};
         b.count = static_cast<int>(std::min<size_t>(kMaxJobs, jobs.size() - c0));
         for (int i = 0; i < b.count; ++i)
             b.j[i] = jobs[c0 + i];
-        auto kern = pass_kernel<TRANS, kMaxNT, false>;
-        ACSC_LAUNCH(tag, kern, dim3(gx, 1, b.count), dim3(256), 0, st, b, np);
+        ACSC_LAUNCH(tag, pass_kernel<NT>, dim3(gx, 1, b.count), dim3(256), 0, st, b, np);
+    }
+}
+
+void launch_unaligned(const char *tag, const std::vector<Job> &jobs, int gx, int np, hipStream_t st)
+{
+    switch (np / 16) {
+    case 1: launch_any<1>(tag, jobs, gx, np, st); break;
+    case 2: launch_any<2>(tag, jobs, gx, np, st); break;
+    case 3: launch_any<3>(tag, jobs, gx, np, st); break;
+    case 4: launch_any<4>(tag, jobs, gx, np, st); break;
+    case 5: launch_any<5>(tag, jobs, gx, np, st); break;
+    case 6: launch_any<6>(tag, jobs, gx, np, st); break;
+    case 7: launch_any<7>(tag, jobs, gx, np, st); break;
+    case 8: launch_any<8>(tag, jobs, gx, np, st); break;
+    case 9: launch_any<9>(tag, jobs, gx, np, st); break;
+    case 10: launch_any<10>(tag, jobs, gx, np, st); break;
+    case 11: launch_any<11>(tag, jobs, gx, np, st); break;
+    default: launch_any<12>(tag, jobs, gx, np, st); break;
     }
 }
 
@@ -1264,7 +1221,7 @@ std::vector<int> plan_splits(const std::vector<Req> &reqs)
 {
     std::vector<int> out(reqs.size(), 1);
     const std::vector<size_t> order = longest_first(reqs);
-    // the DMA jobs are one launch, the element-load jobs another
+    // the DMA jobs are one launch, those over unaligned rows another
     for (int v = 0; v < 2; ++v) {
         std::vector<SplitShape> sh;
         std::vector<size_t> at;
@@ -1291,6 +1248,8 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
     if (NP < 16 || NP % 16 != 0 || NP > SC_KMAX)
         return set_error(ACSC_EINVAL, "pass with %d thin-factor columns (a multiple of 16 up to %d)", NP, SC_KMAX);
     for (const auto &q : reqs) {
+        if (trans && !q.avec)
+            return set_error(ACSC_EINVAL, "pass: the transposed product needs aligned rows");
         if (q.NP != NP)
             return set_error(ACSC_EINVAL, "pass: thin factors of one launch must have the same width");
         if (q.ntc > 0 && (!q.avec || q.ntc != tiles_per_row(trans ? q.M : q.K)))
@@ -1298,7 +1257,7 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
                                           "per tile row");
     }
     const std::vector<size_t> order = longest_first(reqs);
-    std::vector<Job> sj;                 // element-load jobs
+    std::vector<Job> sj;                 // jobs over unaligned rows
     std::vector<const Req *> vq;         // DMA jobs
     std::vector<int> vsplits, vchunk;
     std::vector<RedJob> red;
@@ -1323,18 +1282,13 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
         const int nb = static_cast<int>(cdiv(q.M, kBM) * splits);
         gx = std::max(gx, nb);
         if (splits == 1)
-            sj.push_back(Job{q.A, q.lda, q.Bt, q.ldbt, q.C, q.ldc, 0, q.M, q.K, static_cast<int>(chunk), 1, nb, 0});
+            sj.push_back(Job{q.A, q.lda, q.Bt, q.ldbt, q.C, q.ldc, 0, q.M, q.K, static_cast<int>(chunk), 1, nb});
         else
-            sj.push_back(Job{q.A, q.lda, q.Bt, q.ldbt, q.part, NP, ss, q.M, q.K, static_cast<int>(chunk), splits, nb,
-                             0});
+            sj.push_back(Job{q.A, q.lda, q.Bt, q.ldbt, q.part, NP, ss, q.M, q.K, static_cast<int>(chunk), splits, nb});
     }
     gx = static_cast<int>(round_up(gx, 8));   // block -> XCD placement is the same for every job
-    if (!sj.empty()) {
-        if (trans)
-            launch_scalar<true>(tag, sj, gx, NP, st);
-        else
-            launch_scalar<false>(tag, sj, gx, NP, st);
-    }
+    if (!sj.empty())
+        launch_unaligned(tag, sj, gx, NP, st);
     for (size_t c0 = 0; c0 < vq.size(); c0 += kMaxJobs) {
         const size_t cnt = std::min<size_t>(kMaxJobs, vq.size() - c0);
         std::vector<JobShape> js;

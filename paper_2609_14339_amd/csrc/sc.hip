@@ -10,6 +10,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include "sc_status.h"
 #include "sc_pass.h"
 #include "sc_blend.h"
 #include "sc_chol.h"
@@ -23,8 +24,6 @@
 namespace acsc {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef float nf4 __attribute__((ext_vector_type(4)));
 typedef unsigned int nu4 __attribute__((ext_vector_type(4)));
 
@@ -71,10 +70,9 @@ __device__ __forceinline__ uint16_t from_f32<uint16_t>(float v) { return f32_to_
 //   M <- beta * M + (1 - beta) * G;  M16 <- bf16(M).   With G == NULL only the
 // shadow is written.  The shadow is stored in 64 x 64 tiles (ntc tiles per
 // tile row; see sc_pass.h).
-template <typename GT>
 struct EmaJob {
     float *M;
-    const GT *G;
+    const uint16_t *G;
     int m, n, vec;
     uint16_t *M16;
     int64_t ntc;
@@ -85,12 +83,11 @@ __device__ __forceinline__ int64_t tile_at(int64_t i, int64_t j, int64_t ntc)
     return ((i >> 6) * ntc + (j >> 6)) * 4096 + (i & 63) * 64 + (j & 63);
 }
 
-template <typename GT>
-__global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob<GT>> jb, float beta, float omb)
+__global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob> jb, float beta, float omb)
 {
-    const EmaJob<GT> &J = jb.j[blockIdx.z];
+    const EmaJob &J = jb.j[blockIdx.z];
     float *M = J.M;
-    const GT *G = J.G;
+    const uint16_t *G = J.G;
     const int m = J.m, n = J.n;
     const bool VEC = J.vec != 0;
     uint16_t *M16 = J.M16;
@@ -102,34 +99,52 @@ __global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob<GT>>
         const int64_t i = q / nch;
         const int j0 = static_cast<int>(q - i * nch) * 8;
         float *mr = M + i * n + j0;
-        const GT *gr = G ? G + i * n + j0 : nullptr;
+        const uint16_t *gr = G ? G + i * n + j0 : nullptr;
         float v[8];
-        if (VEC && j0 + 8 <= n) {
-            const nf4 m0 = __builtin_nontemporal_load(reinterpret_cast<const nf4 *>(mr));
-            const nf4 m1 = __builtin_nontemporal_load(reinterpret_cast<const nf4 *>(mr + 4));
-            v[0] = m0.x; v[1] = m0.y; v[2] = m0.z; v[3] = m0.w;
-            v[4] = m1.x; v[5] = m1.y; v[6] = m1.z; v[7] = m1.w;
+        if (j0 + 8 <= n) {
+            if (VEC) {
+                const nf4 m0 = __builtin_nontemporal_load(reinterpret_cast<const nf4 *>(mr));
+                const nf4 m1 = __builtin_nontemporal_load(reinterpret_cast<const nf4 *>(mr + 4));
+                v[0] = m0.x; v[1] = m0.y; v[2] = m0.z; v[3] = m0.w;
+                v[4] = m1.x; v[5] = m1.y; v[6] = m1.z; v[7] = m1.w;
+            } else {
+                // rows of other widths: the same accesses, not 16-byte aligned
+                const F4Any m0 = *reinterpret_cast<const F4Any *>(mr), m1 = *reinterpret_cast<const F4Any *>(mr + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = m0.v[e];
+                    v[4 + e] = m1.v[e];
+                }
+            }
             if (gr) {
                 float g[8];
-                if constexpr (sizeof(GT) == 2) {
+                uint32_t w4[4];
+                if (VEC) {
                     const nu4 gb = __builtin_nontemporal_load(reinterpret_cast<const nu4 *>(gr));
-                    const uint32_t w4[4] = {gb.x, gb.y, gb.z, gb.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        g[2 * e] = __uint_as_float(w4[e] << 16);
-                        g[2 * e + 1] = __uint_as_float(w4[e] & 0xFFFF0000u);
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        w4[e] = gb[e];
                 } else {
-                    const float4 g0 = *reinterpret_cast<const float4 *>(gr);
-                    const float4 g1 = *reinterpret_cast<const float4 *>(gr + 4);
-                    g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w;
-                    g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
+                    const Bf8Any gb = *reinterpret_cast<const Bf8Any *>(gr);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        w4[e] = gb.w[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    g[2 * e] = __uint_as_float(w4[e] << 16);
+                    g[2 * e + 1] = __uint_as_float(w4[e] & 0xFFFF0000u);
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     v[e] = ema_step(v[e], g[e], beta, omb);
-                __builtin_nontemporal_store(nf4{v[0], v[1], v[2], v[3]}, reinterpret_cast<nf4 *>(mr));
-                __builtin_nontemporal_store(nf4{v[4], v[5], v[6], v[7]}, reinterpret_cast<nf4 *>(mr + 4));
+                if (VEC) {
+                    __builtin_nontemporal_store(nf4{v[0], v[1], v[2], v[3]}, reinterpret_cast<nf4 *>(mr));
+                    __builtin_nontemporal_store(nf4{v[4], v[5], v[6], v[7]}, reinterpret_cast<nf4 *>(mr + 4));
+                } else {
+                    *reinterpret_cast<F4Any *>(mr) = F4Any{{v[0], v[1], v[2], v[3]}};
+                    *reinterpret_cast<F4Any *>(mr + 4) = F4Any{{v[4], v[5], v[6], v[7]}};
+                }
             }
             uint16_t h[8];
 #pragma unroll
@@ -142,7 +157,7 @@ __global__ __launch_bounds__(256) void ema_shadow_kernel(const Batch<EmaJob<GT>>
             for (int e = 0; e < 8 && j0 + e < n; ++e) {
                 float x = mr[e];
                 if (gr) {
-                    x = ema_step(x, to_f32<GT>(gr[e]), beta, omb);
+                    x = ema_step(x, bf16_to_f32(gr[e]), beta, omb);
                     mr[e] = x;
                 }
                 M16[tile_at(i, j0 + e, ntc)] = f32_to_bf16(x);
@@ -484,40 +499,18 @@ struct JacJob {
     int *info;
 };
 
-// Status words at the head of a build workspace: the Jacobi sweeps used, the
-// last sweep's largest off-diagonal ratio and the tolerance (float bits), a
-// status (bit 0: the sweep cap was reached above the tolerance; bit 1: the
-// Rayleigh-Ritz phase found no stamp of a subspace phase), and the stamp the
-// subspace phase leaves for the Rayleigh-Ritz phase, which clears it.
-constexpr int kInfoSweeps = 0, kInfoResidual = 1, kInfoTol = 2, kInfoStatus = 3, kInfoStamp = 4, kInfoStall = 5;
-constexpr int kStatusNoConv = 1, kStatusNoSubspace = 2, kStatusStalled = 4;
-// The stamp a subspace phase leaves for its Rayleigh-Ritz phase: the plain
-// one, or the one that also says its fused EMA pass gave up a wait.
-constexpr int kSubspaceStamp = 0x5B5D7A11, kSubspaceStalledStamp = 0x5B5D7A13;
 constexpr int kJacobiMaxSweeps = 40;
-
-// End of a subspace phase: fold the EMA pass's stall word into the stamp and
-// clear it for the next phase.
-__global__ __launch_bounds__(64) void stamp_kernel(const Batch<JacJob> jb)
-{
-    if (threadIdx.x == 0) {
-        int *info = jb.j[blockIdx.z].info;
-        const bool stalled = info[kInfoStall] == pass::kEmaStallMark;
-        info[kInfoStall] = 0;
-        info[kInfoStamp] = stalled ? kSubspaceStalledStamp : kSubspaceStamp;
-    }
-}
-
-constexpr int kJacBlk = 4;   // columns per block
-
-// blocks of the tournament: an even number
-__host__ __device__ constexpr int jacobi_blocks(int k) { return ((k + kJacBlk - 1) / kJacBlk + 1) & ~1; }
 
 // Column pitch of the fp64 kernel in LDS: past the padded rows, so that the
 // lanes that read or write one row of many columns fall on different banks.
 // (The fp32 kernel's 16-byte accesses run best unpadded: 600 us against 850
 // with four more rows at k = 144.)
 __host__ __device__ constexpr int jacobi_pitch_f64(int rows) { return rows + 1; }
+
+constexpr int kJacBlk = 4;   // columns per block
+
+// blocks of the tournament: an even number
+__host__ __device__ constexpr int jacobi_blocks(int k) { return ((k + kJacBlk - 1) / kJacBlk + 1) & ~1; }
 
 // The columns of the factor into LDS (column c at A[c * kp]), rows and columns
 // past k as zeros.  Rows of the factor are read whole, and eight loads go
@@ -1173,26 +1166,6 @@ __global__ __launch_bounds__(256) void tile_bf16_kernel(const Batch<TileJob> jb)
     }
 }
 
-// Xf[i][j] = d_i * X[i][j] * d_j for i, j < r; zero elsewhere (RP x RP).
-struct FilterJob {
-    const float *X;
-    const float *d;
-    float *Xf;
-};
-
-__global__ __launch_bounds__(256) void filter_x_kernel(const Batch<FilterJob> jb, int r, int RP)
-{
-    const float *X = jb.j[blockIdx.z].X;
-    const float *d = jb.j[blockIdx.z].d;
-    float *Xf = jb.j[blockIdx.z].Xf;
-    const int64_t ldx = RP;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= RP * RP)
-        return;
-    const int i = idx / RP, j = idx % RP;
-    Xf[idx] = (i < r && j < r) ? d[i] * X[static_cast<int64_t>(i) * ldx + j] * d[j] : 0.f;
-}
-
 // ---------------------------------------------------------------------------
 // Global-norm clipping of the corrected AdamW step without a pass over
 // G_proj: with U and V orthonormal, X = U^T G V and X_f = d X d,
@@ -1207,7 +1180,7 @@ constexpr int kSumBlocks = 512;
 struct SumJob {
     const void *G;
     int64_t count;    // elements of G (contiguous)
-    int vec;          // 16-byte aligned G and count % 8 == 0: 16-byte loads
+    int vec;          // 16-byte aligned G: 16-byte loads but for the last elements
     double *part;     // [kSumBlocks]
 };
 
@@ -1248,6 +1221,11 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const Batch<SumJob> jb)
                 s += g * g;
             }
             acc += s;
+        }
+        const int64_t i = J.count / V * V + start;
+        if (i < J.count) {
+            const double g = to_f32<GT>(G[i]);
+            acc += g * g;
         }
     } else {
         for (int64_t i = start; i < J.count; i += stride) {
@@ -1343,207 +1321,6 @@ __global__ __launch_bounds__(256) void pad_convert_kernel(const Batch<PadJob<CT>
         const int64_t i = idx / RP;
         const int c = static_cast<int>(idx - i * RP);
         Vc[idx] = from_f32<CT>(c < r ? V[i * r + c] : 0.f);
-    }
-}
-
-template <typename GT>
-struct BlendJob {
-    const GT *G;
-    GT *out;
-    int m, n;
-    const GT *P, *Vc;
-    float *W, *m1, *m2;   // corrected AdamW: fp32 weights and moments, in place
-    float *E;             // error feedback: fp32 memory (holds M), takes M - out
-};
-
-// Element (row, col) of G_proj = gp: stored, or (ADAM) the gradient of the
-// AdamW step of the same element of W (scaled by the call's clip coefficient).
-template <bool ADAM, typename GT>
-__device__ __forceinline__ void blend_out(const BlendJob<GT> &J, int64_t o, float gp, float cf,
-                                          const blend::AdamArgs &ad)
-{
-    if constexpr (ADAM) {
-        float w = J.W[o], m1 = J.m1[o], m2 = J.m2[o];
-        blend::adamw_elem(cf * gp, w, m1, m2, ad);
-        J.W[o] = w;
-        J.m1[o] = m1;
-        J.m2[o] = m2;
-    } else {
-        J.out[o] = from_f32<GT>(gp);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Fused correction pass for bf16 G, 128 x 128 output tiles:
-//   out = alpha * G + (1 - alpha) * P V^T,  P [m, RP], Vc [n, RP] (bf16, RP a
-// multiple of 32, zero padded).
-// The G tile is staged in LDS with 16-byte coalesced loads issued before the
-// products, blended in place in LDS, and written back with 16-byte coalesced
-// stores.  P and V stream through LDS in 32-deep slices.  Four waves, each a
-// 64 x 64 quarter (4 x 4 MFMA tiles).  Tile order: block b runs on XCD b % 8,
-// and XCD x takes the row blocks congruent to x, walking their column blocks,
-// so a row block's slice of P stays in one L2.
-// ---------------------------------------------------------------------------
-constexpr int kBT = 128;              // tile edge
-constexpr int kGPitch = kBT + 8;      // bf16 elements per staged G row (272 bytes)
-constexpr int kKPitch = 32 + 8;       // P / V slice rows (80 bytes)
-
-template <bool VEC, bool ADAM>
-__global__ __launch_bounds__(256) void blend16_kernel(const Batch<BlendJob<uint16_t>> jb, int RP, float alpha,
-                                                      int col_blocks_max, const blend::AdamArgs ad)
-{
-    const BlendJob<uint16_t> &J = jb.j[blockIdx.z];
-    const int m = J.m, n = J.n;
-    const int rb_n = (m + kBT - 1) / kBT, cb_n = (n + kBT - 1) / kBT;
-    // XCD-aware tile order
-    const int b = blockIdx.x;
-    const int xcd = b & 7, t = b >> 3;
-    const int rb = xcd + 8 * (t / cb_n);
-    const int cb = t % cb_n;
-    (void)col_blocks_max;
-    if (rb >= rb_n)
-        return;
-    const int row0 = rb * kBT, col0 = cb * kBT;
-    // one LDS region: P / V slices during the products, then the G tile
-    __shared__ __attribute__((aligned(16))) uint16_t sm[kBT * kGPitch];
-    uint16_t *Ps = sm;
-    uint16_t *Vs = sm + kBT * kKPitch;
-    uint16_t *Gs = sm;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint16_t *G = J.G;
-    uint16_t *out = J.out;
-    // G tile into registers now (128 rows x 16 chunks; 8 chunks per thread),
-    // so its latency overlaps the products
-    uint4 gr[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int q = tid + 256 * u;
-        const int rr = q >> 4, c8 = (q & 15) * 8;
-        const int gi = row0 + rr, gj = col0 + c8;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (gi < m) {
-            const uint16_t *src = G + static_cast<int64_t>(gi) * n + gj;
-            if (VEC && gj + 8 <= n) {
-                v = *reinterpret_cast<const uint4 *>(src);
-            } else {
-                uint16_t e8[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    e8[e] = (gj + e < n) ? src[e] : uint16_t(0);
-                __builtin_memcpy(&v, e8, sizeof(v));
-            }
-        }
-        gr[u] = v;
-    }
-    // P / V slices: 2 x 128 rows x 4 chunks; 4 chunks per thread, prefetched
-    uint4 pv[4];
-    auto load_slice = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = tid + 256 * u;
-            const bool isV = q >= kBT * 4;
-            const int qq = isV ? q - kBT * 4 : q;
-            const int rr = qq >> 2, c8 = (qq & 3) * 8;
-            const int g = (isV ? col0 : row0) + rr;
-            const int lim = isV ? n : m;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (g < lim)
-                v = *reinterpret_cast<const uint4 *>((isV ? J.Vc : J.P) + static_cast<int64_t>(g) * RP + k0 + c8);
-            pv[u] = v;
-        }
-    };
-    const int wr = wave >> 1, wc = wave & 1;
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            acc[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    load_slice(0);
-    for (int k0 = 0; k0 < RP; k0 += 32) {
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = tid + 256 * u;
-            const bool isV = q >= kBT * 4;
-            const int qq = isV ? q - kBT * 4 : q;
-            const int rr = qq >> 2, c8 = (qq & 3) * 8;
-            *reinterpret_cast<uint4 *>(&(isV ? Vs : Ps)[rr * kKPitch + c8]) = pv[u];
-        }
-        __syncthreads();
-        if (k0 + 32 < RP)
-            load_slice(k0 + 32);
-        bf16x8 af[4], bfr[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            af[a] = *reinterpret_cast<const bf16x8 *>(&Ps[(wr * 64 + a * 16 + (lane & 15)) * kKPitch + (lane >> 4) * 8]);
-            bfr[a] = *reinterpret_cast<const bf16x8 *>(&Vs[(wc * 64 + a * 16 + (lane & 15)) * kKPitch + (lane >> 4) * 8]);
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[c], acc[a][c], 0, 0, 0);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int q = tid + 256 * u;
-        const int rr = q >> 4, c8 = (q & 15) * 8;
-        *reinterpret_cast<uint4 *>(&Gs[rr * kGPitch + c8]) = gr[u];
-    }
-    __syncthreads();
-    // blend in place in the staged tile
-    const float oma = 1.0f - alpha;
-    if constexpr (ADAM) {
-        // the blended values are the AdamW gradient, never stored
-        const float cf = *ad.coef;
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int cc = wc * 64 + c * 16 + (lane & 15);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int rr = wr * 64 + a * 16 + (lane >> 4) * 4 + e;
-                    const int gi = row0 + rr, gj = col0 + cc;
-                    if (gi < m && gj < n)
-                        blend_out<true>(J, static_cast<int64_t>(gi) * n + gj,
-                                        blend_step(bf16_to_f32(Gs[rr * kGPitch + cc]), acc[a][c][e], alpha, oma), cf, ad);
-                }
-            }
-        return;
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int cc = wc * 64 + c * 16 + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int rr = wr * 64 + a * 16 + (lane >> 4) * 4 + e;
-                uint16_t &gv = Gs[rr * kGPitch + cc];
-                gv = f32_to_bf16(blend_step(bf16_to_f32(gv), acc[a][c][e], alpha, oma));
-            }
-        }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int q = tid + 256 * u;
-        const int rr = q >> 4, c8 = (q & 15) * 8;
-        const int gi = row0 + rr, gj = col0 + c8;
-        if (gi >= m)
-            continue;
-        uint16_t *dst = out + static_cast<int64_t>(gi) * n + gj;
-        const uint4 v = *reinterpret_cast<const uint4 *>(&Gs[rr * kGPitch + c8]);
-        if (VEC && gj + 8 <= n) {
-            *reinterpret_cast<uint4 *>(dst) = v;
-        } else {
-            uint16_t e8[8];
-            __builtin_memcpy(e8, &v, sizeof(e8));
-            for (int e = 0; e < 8 && gj + e < n; ++e)
-                dst[e] = e8[e];
-        }
     }
 }
 
@@ -1846,8 +1623,10 @@ void gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::
 // 1e-7 * cond(Y); the iteration only needs a well-conditioned basis, and the
 // final basis gets the second pass.  The last pass also writes the bf16
 // transposed copy that the next streaming pass reads.
-// `splits`: as for gram().
-int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::vector<int> splits, hipStream_t st)
+// `splits`: as for gram().  `last`: this is the last basis of a subspace phase,
+// whose kernel also stamps the workspace.
+int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::vector<int> splits, bool last,
+                   hipStream_t st)
 {
     const Dims &d0 = ms[0].D;
     std::vector<float *> A;
@@ -1871,7 +1650,8 @@ int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::
             float *Y = A[i];
             uint16_t *t16 = (use16 && pass + 1 == passes) ? (onY ? ms[i].pw.Yt16 : ms[i].pw.Zt16) : nullptr;
             const int64_t ldt = onY ? ms[i].pw.ldy16 : ms[i].pw.ldz16;
-            g.push_back(orth::Req{Y, rows[i], ms[i].pw.T, t16, ldt, !use16 || passes == 2});
+            g.push_back(orth::Req{Y, rows[i], ms[i].pw.T, t16, ldt, !use16 || passes == 2,
+                                  last && pass + 1 == passes ? ms[i].pw.info : nullptr});
         }
         if (int rc = orth::run("sc_orth_apply", g, d0.KP, st))
             return rc;
@@ -1901,14 +1681,14 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
     const bool fused = use16 && pass::ema_fusable(er);
     if ((phases & kPhaseSubspace) && !fused) {
         if (use16) {
-            std::vector<EmaJob<uint16_t>> j;
+            std::vector<EmaJob> j;
             int64_t tot = 1;
             for (auto &m : ms) {
-                j.push_back(EmaJob<uint16_t>{m.in->M, static_cast<const uint16_t *>(m.in->G), m.D.m, m.D.n,
+                j.push_back(EmaJob{m.in->M, static_cast<const uint16_t *>(m.in->G), m.D.m, m.D.n,
                                              (m.D.n % 8) == 0 ? 1 : 0, m.pw.M16, m.pw.ntc16});
                 tot = std::max<int64_t>(tot, static_cast<int64_t>(m.D.m) * cdiv(m.D.n, 8));
             }
-            launch_jobs("sc_ema", ema_shadow_kernel<uint16_t>, j, dim3(grid1d(tot)), dim3(256), 0, st, beta, omb);
+            launch_jobs("sc_ema", ema_shadow_kernel, j, dim3(grid1d(tot)), dim3(256), 0, st, beta, omb);
         } else {
             std::vector<Ema32Job<float>> j;
             int64_t tot = 1;
@@ -1976,25 +1756,21 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         rc = fused ? pass::ema_run("sc_ema", er, beta, omb, st) : pass(true);
         if (rc)
             return rc;
-        if ((rc = orthonormalise(ms, true, power_iters == 0 ? 2 : 1, use16, splits, st)))
+        if ((rc = orthonormalise(ms, true, power_iters == 0 ? 2 : 1, use16, splits, power_iters == 0, st)))
             return rc;
         for (int it = 0; it < power_iters; ++it) {
             if ((rc = pass(false)))
                 return rc;
-            if ((rc = orthonormalise(ms, false, 1, use16, splits, st)))
+            if ((rc = orthonormalise(ms, false, 1, use16, splits, false, st)))
                 return rc;
             if ((rc = pass(true)))
                 return rc;
-            if ((rc = orthonormalise(ms, true, it + 1 == power_iters ? 2 : 1, use16, splits, st)))
+            if ((rc = orthonormalise(ms, true, it + 1 == power_iters ? 2 : 1, use16, splits, it + 1 == power_iters, st)))
                 return rc;
         }
         // Z = M^T Q (= B^T) for the Rayleigh-Ritz step: B B^T = Z^T Z = L L^T, SVD of L by Jacobi.
         if ((rc = pass(false)))
             return rc;
-        std::vector<JacJob> sj;
-        for (auto &m : ms)
-            sj.push_back(JacJob{nullptr, nullptr, nullptr, nullptr, nullptr, m.pw.info});
-        launch_jobs("sc_stamp", stamp_kernel, sj, dim3(1), dim3(64), 0, st);
     }
     if (!(phases & kPhaseRitz))
         return ACSC_OK;
@@ -2043,7 +1819,7 @@ void clip_norm(const std::vector<Mat> &ms, int r, float alpha, const AdamCtx &ad
     std::vector<SumJob> sj;
     for (const Mat &m : ms) {
         const int64_t cnt = static_cast<int64_t>(m.D.m) * m.D.n;
-        const bool vec = aligned(m.in->G, 16) && cnt % (16 / sizeof(GT)) == 0;
+        const bool vec = aligned(m.in->G, 16);
         sj.push_back(SumJob{m.in->G, cnt, vec ? 1 : 0, m.cw.sq});
     }
     launch_jobs("sc_sumsq", sumsq_kernel<GT>, sj, dim3(kSumBlocks), dim3(256), 0, st);
@@ -2092,20 +1868,14 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
         if (int rc = f32::pass("sc_gv", false, q, st))
             return rc;
     }
-    // X = U^T T   [r, RP]
+    // X = U^T T   [r, RP], and X_f = d X d   [RP, RP], zero-padded
     {
         std::vector<orth::InnerReq> iq;
         for (auto &m : ms)
             iq.push_back(orth::InnerReq{m.in->U, r, m.cw.Tm, RP, m.D.m, r, RP, m.cw.X, RP, m.cw.xpart,
-                                        split_count(m.D.r, m.D.m)});
+                                        split_count(m.D.r, m.D.m), m.in->d, m.cw.Xf});
         if (int rc = orth::inner("sc_utt", iq, st))
             return rc;
-    }
-    {
-        std::vector<FilterJob> f;
-        for (auto &m : ms)
-            f.push_back(FilterJob{m.cw.X, m.in->d, m.cw.Xf});
-        launch_jobs("sc_filter", filter_x_kernel, f, dim3(grid1d(int64_t(RP) * RP)), dim3(256), 0, st, r, RP);
     }
     // P = U X_f  [m, RP] in the compute type; V in the compute type [n, RP]
     {
@@ -2130,41 +1900,13 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
     const char *btag = adam ? "sc_blend_adamw" : "sc_blend";
     {
         if constexpr (sizeof(GT) == 2) {
-            if (blend::supported(RP)) {
-                std::vector<blend::Req> q;
-                for (auto &m : ms)
-                    q.push_back(blend::Req{static_cast<const uint16_t *>(m.in->G), static_cast<uint16_t *>(m.in->G_proj),
-                                           m.D.m, m.D.n, static_cast<const uint16_t *>(m.cw.Pc),
-                                           static_cast<const uint16_t *>(m.cw.Vc), m.ad ? m.ad->W : nullptr,
-                                           m.ad ? m.ad->m1 : nullptr, m.ad ? m.ad->m2 : nullptr, nullptr});
-                return blend::run(btag, q, RP, alpha, st, adam ? &ad : nullptr);
-            }
-            // 128 x 128 tiles, XCD-aware order (see blend16_kernel)
-            std::vector<BlendJob<GT>> bj;
+            std::vector<blend::Req> q;
             for (auto &m : ms)
-                bj.push_back(BlendJob<GT>{static_cast<const GT *>(m.in->G), static_cast<GT *>(m.in->G_proj), m.D.m, m.D.n,
-                                          static_cast<const GT *>(m.cw.Pc), static_cast<const GT *>(m.cw.Vc),
-                                          m.ad ? m.ad->W : nullptr, m.ad ? m.ad->m1 : nullptr,
-                                          m.ad ? m.ad->m2 : nullptr, nullptr});
-            int tiles = 1, cbm = 1;
-            bool vec = true;
-            for (auto &m : ms) {
-                const int rbn = static_cast<int>(cdiv(m.D.m, kBT)), cbn = static_cast<int>(cdiv(m.D.n, kBT));
-                tiles = std::max(tiles, static_cast<int>(round_up(rbn, 8)) * cbn);
-                cbm = std::max(cbm, cbn);
-                vec = vec && (m.D.n % 8) == 0 && aligned(m.in->G, 16) && (adam || aligned(m.in->G_proj, 16));
-            }
-            if (adam) {
-                if (vec)
-                    launch_jobs(btag, blend16_kernel<true, true>, bj, dim3(tiles), dim3(256), 0, st, RP, alpha, cbm, ad);
-                else
-                    launch_jobs(btag, blend16_kernel<false, true>, bj, dim3(tiles), dim3(256), 0, st, RP, alpha, cbm, ad);
-            } else {
-                if (vec)
-                    launch_jobs(btag, blend16_kernel<true, false>, bj, dim3(tiles), dim3(256), 0, st, RP, alpha, cbm, ad);
-                else
-                    launch_jobs(btag, blend16_kernel<false, false>, bj, dim3(tiles), dim3(256), 0, st, RP, alpha, cbm, ad);
-            }
+                q.push_back(blend::Req{static_cast<const uint16_t *>(m.in->G), static_cast<uint16_t *>(m.in->G_proj),
+                                       m.D.m, m.D.n, static_cast<const uint16_t *>(m.cw.Pc),
+                                       static_cast<const uint16_t *>(m.cw.Vc), m.ad ? m.ad->W : nullptr,
+                                       m.ad ? m.ad->m1 : nullptr, m.ad ? m.ad->m2 : nullptr, nullptr});
+            return blend::run(btag, q, RP, alpha, st, adam ? &ad : nullptr);
         } else {
             std::vector<f32::BlendReq> q;
             for (auto &m : ms)
@@ -2244,14 +1986,6 @@ __global__ __launch_bounds__(256) void crop_kernel(const Batch<CropJob> jb)
     }
 }
 
-// Padded rank of the decompression: the streamed-tile widths for bf16.
-int psgd_rp(int r, bool use16)
-{
-    if (!use16)
-        return static_cast<int>(round_up(r, 32));
-    return r <= 64 ? 64 : (r <= 128 ? 128 : 192);
-}
-
 struct PsgdWs {
     PriorWs pw;     // M16, Zt16 (Q^T bf16), Y (P, P_hat), Yt16 (P_hat^T bf16), Z (Q'), part, T, gram
     void *Pc, *Vc;  // decompression factors [m, RPd], [n, RPd] in the compute type
@@ -2264,7 +1998,7 @@ size_t carve_psgd(const Dims &d, acsc_dtype dt, void *base, PsgdWs *w)
     PsgdWs t;
     Carve c(base);
     c.off = carve_prior(d, use16, base, &t.pw);
-    t.RPd = psgd_rp(d.r, use16);
+    t.RPd = d.RP;
     const size_t es = dtype_size(dt);
     t.Pc = c.take<unsigned char>(static_cast<size_t>(d.m) * t.RPd * es);
     t.Vc = c.take<unsigned char>(static_cast<size_t>(d.n) * t.RPd * es);
@@ -2313,17 +2047,17 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
             if (int rc = pass::ema_run("psgd_feedback_mq", er, 1.0f, 1.0f, st))
                 return rc;
         } else {
-            std::vector<EmaJob<uint16_t>> j;
+            std::vector<EmaJob> j;
             std::vector<pass::Req> q;
             int64_t tot = 1;
             for (auto &x : it) {
-                j.push_back(EmaJob<uint16_t>{x.in->E, static_cast<const uint16_t *>(x.in->G), x.in->m, x.in->n,
+                j.push_back(EmaJob{x.in->E, static_cast<const uint16_t *>(x.in->G), x.in->m, x.in->n,
                                              (x.in->n % 8) == 0 ? 1 : 0, x.w.pw.M16, x.w.pw.ntc16});
                 tot = std::max<int64_t>(tot, static_cast<int64_t>(x.in->m) * cdiv(x.in->n, 8));
                 q.push_back(pass::Req{x.w.pw.M16, 0, true, x.w.pw.Zt16, x.w.pw.ldz16, x.w.pw.Y, KP,
                                       x.in->m, x.in->n, KP, x.w.pw.part, static_cast<int>(x.w.pw.ntc16)});
             }
-            launch_jobs("psgd_feedback", ema_shadow_kernel<uint16_t>, j, dim3(grid1d(tot)), dim3(256), 0, st, 1.0f,
+            launch_jobs("psgd_feedback", ema_shadow_kernel, j, dim3(grid1d(tot)), dim3(256), 0, st, 1.0f,
                         1.0f);
             if (int rc = pass::run("psgd_pass_mq", false, q, st, splits.data()))
                 return rc;
@@ -2370,7 +2104,7 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
     for (auto &x : it)
         ms.push_back(x.mat);
     // CholeskyQR2: Y <- P_hat (fp32), and its bf16 transposed copy for the pass
-    if (int rc = orthonormalise(ms, true, 2, use16, std::vector<int>(ms.size(), 1), st))
+    if (int rc = orthonormalise(ms, true, 2, use16, std::vector<int>(ms.size(), 1), false, st))
         return rc;
     std::vector<CropJob> cj;
     for (auto &x : it)

@@ -50,10 +50,7 @@ __device__ __forceinline__ void adamw_elem(float g, float &w, float &m1, float &
     w = w * a.wdf - a.step * m1 / (__builtin_sqrtf(m2) * a.isbc2 + a.eps);
 }
 
-// Whether the streamed-tile kernel handles this padded rank.
-bool supported(int RP);
-
-// Enqueue the blend of every request (all share RP) on `st`; with `adam`,
+// Enqueue the blend of every request (all share RP, a multiple of 32) on `st`; with `adam`,
 // G_proj is not stored and the requests' W, m1, m2 take the AdamW step.
 int run(const char *tag, const std::vector<Req> &reqs, int RP, float alpha, hipStream_t st,
         const AdamArgs *adam = nullptr);

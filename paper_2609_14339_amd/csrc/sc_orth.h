@@ -21,6 +21,7 @@ struct Req {
     uint16_t *Qt16;      // [KP, ldq] bf16 (Q^T), or nullptr
     int64_t ldq;         // a multiple of 8
     bool write32;        // store Q over Y
+    int *stamp;          // status words of a workspace to stamp (stamp_subspace), or nullptr
 };
 
 // Enqueue Q = Y T for every request (all share KP, a multiple of 16 up to
@@ -59,6 +60,8 @@ struct InnerReq {
     int64_t ldc;
     float *part;
     int part_blocks;
+    const float *d;      // [NA], or nullptr: no filtered copy
+    float *Cf;           // [NB, NB]: d_i C[i][j] d_j for i, j < NA, zero elsewhere
 };
 
 // Alignment as for gemm(), NB a multiple of 4.

@@ -20,6 +20,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "sc_status.h"
+
 namespace acsc {
 namespace pass {
 
@@ -84,10 +86,10 @@ struct EmaReq {
     int *stall;           // set to kEmaStallMark if a wait of the kernel ran out of polls, or nullptr
 };
 
-// What the fused kernel writes to EmaReq::stall when one of its bounded waits
-// for the other waves of a workgroup gave up (that workgroup's products are
-// then not to be trusted); nothing is written otherwise.
-constexpr int kEmaStallMark = 0x57A11ED0;
+// (kEmaStallMark, in sc_status.h, is what the fused kernel writes to
+// EmaReq::stall when one of its bounded waits for the other waves of a
+// workgroup gave up: that workgroup's products are then not to be trusted.
+// Nothing is written otherwise.)
 // Polls of a wait before it gives up (each about a microsecond or less).  The
 // environment variable ACSC_EMA_SPIN_LIMIT, read by each call, lowers it (0
 // gives up at the first unmet check), so that the report can be exercised.

@@ -110,6 +110,16 @@ def test_bf16_padded_ranks_off_the_tile_kernel(pk, m, n, r):
     _compare(cases, got, ref, 2e-2)
 
 
+@pytest.mark.parametrize("m,n,r", [(257, 1003, 20), (300, 515, 70), (129, 1021, 100), (140, 333, 133)])
+def test_bf16_rows_of_odd_width(pk, m, n, r):
+    # whole chunks of unaligned rows take 16-byte accesses, the last one elements
+    cases = [_case(m, n, r, 30 + r, torch.bfloat16, 5), _case(m + 5, n + 4, r, 31 + r, torch.bfloat16, 5)]
+    got, N = _run(pk, cases, r, 0.3, 5, 2.0, torch.bfloat16)
+    ref, No = _oracle(cases, 0.3, 5, 2.0)
+    assert abs(N - No) <= 5e-3 * No
+    _compare(cases, got, ref, 2e-2)
+
+
 @pytest.mark.parametrize("misalign", [False, True])
 @pytest.mark.parametrize("m,n,r", [(512, 384, 64), (256, 1024, 128), (400, 264, 150)])
 def test_bf16_streamed_tile_kernel(pk, m, n, r, misalign):

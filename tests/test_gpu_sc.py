@@ -81,7 +81,7 @@ def test_correct_ragged_shapes(pk, dtype, m, n, r):
 
 
 @pytest.mark.parametrize("m,n,r", [(130, 260, 64), (257, 1003, 50), (129, 515, 128), (200, 333, 190), (300, 1001, 24),
-                                   (140, 452, 80)])
+                                   (140, 452, 80), (1000, 4099, 150), (4097, 1101, 73), (513, 2049, 160)])
 def test_correct_stores_widths_that_are_no_multiple_of_8(pk, m, n, r):
     """bf16 rows that are not 16-byte aligned take the element-wise stores of
     the blend at every padded rank; the output starts as NaN, so an element
