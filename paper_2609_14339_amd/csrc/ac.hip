@@ -861,51 +861,64 @@ __global__ __launch_bounds__(64 * kBernWaves) void bern_mask_kernel(int64_t rows
 }
 
 // One workgroup: row_ptr[1 ..] holds the row counts; it becomes their
-// inclusive prefix sum, row_ptr[0] = 0.  Tiles of 4096 rows: thread t loads
-// rows t, t + 1024, .. of the tile (coalesced), the tile is scanned in LDS in
-// a fixed order, and the running total carries to the next tile.
+// inclusive prefix sum, row_ptr[0] = 0.  Tiles of 16384 rows: thread t loads
+// rows t, t + 1024, .. of the tile (coalesced, all in flight at once), then
+// sums its run of 16 consecutive rows; waves scan their threads' sums by lane
+// shifts and meet once to add up the waves before them, and the running
+// total carries to the next tile.  Within a tile sums fit 31 bits (a count is
+// at most 65536).  A chain of latencies bounds it: 16384 rows took 18 us in
+// tiles of 4096 with a barrier pair per doubling of the scan, 7 us so.
 __global__ __launch_bounds__(1024) void bern_scan_kernel(int64_t rows, int64_t *__restrict__ row_ptr)
 {
-    constexpr int kTile = 4096;
-    __shared__ int64_t v[kTile];
-    __shared__ int64_t part[1024];
-    const int t = threadIdx.x;
+    constexpr int kRun = 16, kTile = 1024 * kRun;
+    // thread t's run starts at t (kRun + 1): runs in distinct banks
+    __shared__ int32_t v[1024 * (kRun + 1)];
+    __shared__ int32_t wsum[16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    auto at = [](int i) { return i + i / kRun; };
     int64_t carry = 0;
     for (int64_t r0 = 0; r0 < rows; r0 += kTile) {
         const int n = static_cast<int>(min<int64_t>(kTile, rows - r0));
+        int64_t c[kRun];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = t + 1024 * k;
-            v[i] = i < n ? row_ptr[r0 + i + 1] : 0;
-        }
+        for (int k = 0; k < kRun; ++k)
+            c[k] = row_ptr[r0 + min(t + 1024 * k, n - 1) + 1];
+#pragma unroll
+        for (int k = 0; k < kRun; ++k)
+            v[at(t + 1024 * k)] = t + 1024 * k < n ? static_cast<int32_t>(c[k]) : 0;
         __syncthreads();
-        // thread t scans its run of four, then the 1024 run sums
-        int64_t s = 0;
+        int32_t run[kRun], s = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            s += v[4 * t + k];
-            v[4 * t + k] = s;
+        for (int k = 0; k < kRun; ++k) {
+            s += v[at(kRun * t + k)];
+            run[k] = s;
         }
-        part[t] = s;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const int64_t x = t >= off ? part[t - off] : 0;
-            __syncthreads();
-            part[t] += x;
-            __syncthreads();
+        int32_t inc = s;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t x = __shfl_up(inc, off, 64);
+            inc += lane >= off ? x : 0;
         }
-        const int64_t before = carry + (t ? part[t - 1] : 0);
+        if (lane == 63)
+            wsum[wave] = inc;
+        __syncthreads();
+        int32_t before = inc - s, total = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            v[4 * t + k] += before;
-        carry += part[1023];
+        for (int w = 0; w < 16; ++w) {
+            before += w < wave ? wsum[w] : 0;
+            total += wsum[w];
+        }
+#pragma unroll
+        for (int k = 0; k < kRun; ++k)
+            v[at(kRun * t + k)] = before + run[k];
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < kRun; ++k) {
             const int i = t + 1024 * k;
             if (i < n)
-                row_ptr[r0 + i + 1] = v[i];
+                row_ptr[r0 + i + 1] = carry + v[at(i)];
         }
+        carry += total;
         __syncthreads();
     }
     if (t == 0)

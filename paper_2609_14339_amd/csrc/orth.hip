@@ -53,6 +53,7 @@ struct Job {
     int nwrite;
     uint16_t *Ct16;
     int64_t ldq;
+    int nt;           // rows of Ct16
     int *stamp;
 };
 struct Batch {
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(256) void tall_small_kernel(const Batch jb)
         const int64_t ldq = J.ldq;
         for (int idx = tid; idx < TP * (kRows / 8); idx += 256) {
             const int col = idx / (kRows / 8), r8 = (idx % (kRows / 8)) * 8;
-            if (col < nwrite && row0 + r8 < rows)
+            if (col < J.nt && row0 + r8 < rows)
                 *reinterpret_cast<uint4 *>(Q + col * ldq + row0 + r8) =
                     *reinterpret_cast<const uint4 *>(St + col * kSP + r8);
         }
@@ -488,8 +489,8 @@ int run(const char *tag, const std::vector<Req> &reqs, int KP, hipStream_t st)
             return set_error(ACSC_EINVAL, "orth: bf16 copy needs 16-byte rows of at least %d entries", q.rows);
         if (!aligned(q.Y, 16) || !aligned(q.T, 16))
             return set_error(ACSC_EINVAL, "orth: Y and T must be 16-byte aligned");
-        jobs.push_back(Job{q.Y, KP, q.rows, KP, q.T, KP, KP, 1, q.write32 ? q.Y : nullptr, nullptr, KP, KP,
-                           q.Qt16, q.ldq, q.stamp});
+        jobs.push_back(Job{q.Y, KP, q.rows, KP, q.T, KP, KP, 1, q.out ? q.out : q.write32 ? q.Y : nullptr, nullptr,
+                           q.out ? q.ldo : KP, q.out ? q.nout : KP, q.Qt16, q.ldq, KP, q.stamp});
     }
     return launch_all(tag, jobs, st);
 }
@@ -519,7 +520,7 @@ int gemm(const char *tag, const std::vector<GemmReq> &reqs, hipStream_t st)
         if (q.rows < 1)
             continue;
         jobs.push_back(Job{q.A, q.lda, q.rows, q.K, q.B, q.ldb, q.N, 0, q.C32, q.C16, q.ldc, q.nwrite, nullptr, 0,
-                           nullptr});
+                           0, nullptr});
     }
     return launch_all(tag, jobs, st);
 }

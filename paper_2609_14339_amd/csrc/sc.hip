@@ -1123,22 +1123,28 @@ __global__ __launch_bounds__(256) void tile_bf16_kernel(const Batch<TileJob> jb)
     constexpr int kPitch = kKMax + 2;
     __shared__ __attribute__((aligned(16))) uint16_t Ts[kTileRows * kPitch];
     const int CP = J.CP;
-    // wave w fills rows w, w + 4, ..., its lanes 64 consecutive columns
+    // wave w fills rows w, w + 4, ..., its lanes 64 consecutive columns; a
+    // lane's 16 values of a column leave memory together (one at a time, each
+    // waits for its own load: 13.7 us for the V of an 8B-class layer at rank
+    // 64, 7.7 us so)
     const int cl = threadIdx.x & 63, rg = threadIdx.x >> 6;
-    for (int r = rg; r < kTileRows; r += 4) {
-        const int64_t i = row0 + r;
-        for (int c = cl; c < CP; c += 64) {
-            float v = 0.f;
-            if (i < J.rows && c < J.cols) {
-                if (J.X)
-                    v = J.X[i * J.ldx + c];
-                else if (J.Vw && c < J.rw)
-                    v = J.Vw[i * J.rw + c];
-                else
-                    v = start_uniform(J.seed, i, c);
-            }
-            Ts[r * kPitch + c] = f32_to_bf16(v);
+    constexpr int RPT = kTileRows / 4;
+    for (int c = cl; c < CP; c += 64) {
+        float v[RPT];
+        const float *src = J.X ? J.X : J.Vw && c < J.rw ? J.Vw : nullptr;
+        const int64_t ld = J.X ? J.ldx : J.rw;
+        if (src && c < J.cols) {
+#pragma unroll
+            for (int u = 0; u < RPT; ++u)
+                v[u] = src[static_cast<int64_t>(min(row0 + rg + 4 * u, J.rows - 1)) * ld + c];
+        } else {
+#pragma unroll
+            for (int u = 0; u < RPT; ++u)
+                v[u] = c < J.cols ? start_uniform(J.seed, row0 + rg + 4 * u, c) : 0.f;
         }
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            Ts[(rg + 4 * u) * kPitch + c] = f32_to_bf16(row0 + rg + 4 * u < J.rows ? v[u] : 0.f);
     }
     __syncthreads();
     if (J.Xc) {
@@ -1534,6 +1540,7 @@ struct Mat {
     CorrWs cw;
     uint64_t seed;
     const sc_adamw_state *ad = nullptr;   // corrected AdamW: this matrix's optimiser state
+    float *q32 = nullptr;                 // PowerSGD: the final basis goes here (r columns) and not over Y
 };
 
 // Corrected AdamW: the epilogue constants and the call's norm accumulator.
@@ -1650,7 +1657,8 @@ int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::
             float *Y = A[i];
             uint16_t *t16 = (use16 && pass + 1 == passes) ? (onY ? ms[i].pw.Yt16 : ms[i].pw.Zt16) : nullptr;
             const int64_t ldt = onY ? ms[i].pw.ldy16 : ms[i].pw.ldz16;
-            g.push_back(orth::Req{Y, rows[i], ms[i].pw.T, t16, ldt, !use16 || passes == 2,
+            float *out = pass + 1 == passes ? ms[i].q32 : nullptr;
+            g.push_back(orth::Req{Y, rows[i], ms[i].pw.T, t16, ldt, !use16 || passes == 2, out, ms[i].D.r, ms[i].D.r,
                                   last && pass + 1 == passes ? ms[i].pw.info : nullptr});
         }
         if (int rc = orth::run("sc_orth_apply", g, d0.KP, st))
@@ -2029,7 +2037,9 @@ CropJob crop_of(const PsgdItem &x, const float *src, int rows, float *dst, int r
     return CropJob{splits > 1 ? x.w.pw.part : src, KP, dst, rows, r, splits, static_cast<int64_t>(rows) * KP};
 }
 
-int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t st)
+// With `left` (the whole step) P stays in the workspace: in Y, or in the
+// partials that `left` counts; otherwise it goes to the caller's factor.
+int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, std::vector<int> *left, hipStream_t st)
 {
     const int KP = it[0].mat.D.KP;
     std::vector<int> splits(it.size(), 1);
@@ -2081,6 +2091,10 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
         if (int rc = f32::pass("psgd_pass_mq", false, q, st, splits.data()))
             return rc;
     }
+    if (left) {
+        *left = splits;
+        return ACSC_OK;
+    }
     std::vector<CropJob> cj;
     for (size_t i = 0; i < it.size(); ++i)
         cj.push_back(crop_of(it[i], it[i].w.pw.Y, it[i].in->m, it[i].in->P, r, splits[i]));
@@ -2088,10 +2102,12 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t
     return ACSC_OK;
 }
 
-int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipStream_t st)
+// `left`: what psgd_project_phase left of P; nullptr: P is the caller's.
+int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, const std::vector<int> *left,
+                             hipStream_t st)
 {
     const int KP = it[0].mat.D.KP;
-    {
+    if (!left) {
         std::vector<PadJob<float>> pj;
         int64_t tp = 1;
         for (auto &x : it) {
@@ -2101,15 +2117,21 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
         launch_jobs("psgd_pconvert", pad_convert_kernel<float>, pj, dim3(grid1d(tp)), dim3(256), 0, st, r, KP);
     }
     std::vector<Mat> ms;
-    for (auto &x : it)
+    for (auto &x : it) {
         ms.push_back(x.mat);
-    // CholeskyQR2: Y <- P_hat (fp32), and its bf16 transposed copy for the pass
-    if (int rc = orthonormalise(ms, true, 2, use16, std::vector<int>(ms.size(), 1), false, st))
+        if (use16)
+            ms.back().q32 = x.in->P;   // the pass below reads the bf16 copy only
+    }
+    // CholeskyQR2: P_hat (fp32), and its bf16 transposed copy for the pass
+    if (int rc = orthonormalise(ms, true, 2, use16, left ? *left : std::vector<int>(ms.size(), 1), false, st))
         return rc;
     std::vector<CropJob> cj;
-    for (auto &x : it)
-        cj.push_back(crop_of(x, x.w.pw.Y, x.in->m, x.in->P, r, 1));
-    crop("psgd_crop", cj, st);
+    if (!use16) {
+        for (auto &x : it)
+            cj.push_back(crop_of(x, x.w.pw.Y, x.in->m, x.in->P, r, 1));
+        crop("psgd_crop", cj, st);
+        cj.clear();
+    }
     std::vector<int> splits(it.size(), 1);
     if (use16) {
         std::vector<pass::Req> q;
@@ -2126,7 +2148,6 @@ int psgd_orthogonalize_phase(std::vector<PsgdItem> &it, bool use16, int r, hipSt
         if (int rc = f32::pass("psgd_pass_mtp", true, q, st, splits.data()))
             return rc;
     }
-    cj.clear();
     for (size_t i = 0; i < it.size(); ++i)
         cj.push_back(crop_of(it[i], it[i].w.pw.Z, it[i].in->n, it[i].in->Q, r, splits[i]));
     crop("psgd_crop", cj, st);
@@ -2215,11 +2236,14 @@ int psgd_run(int count, const psgd_matrix *mats, acsc_dtype dt, int r, int phase
     const bool use16 = dt == ACSC_BF16;
     if (int rc = chol::prepare(it[0].mat.D.KP))
         return rc;
+    // within one step nothing else reads P = M Q: it need not go through the
+    // caller's factor (two launches of about 4.5 us per group of equal rank)
     int rc = ACSC_OK;
+    std::vector<int> left;
     if (phase == 0 || phase == 3)
-        rc = psgd_project_phase(it, use16, r, st);
+        rc = psgd_project_phase(it, use16, r, phase == 3 ? &left : nullptr, st);
     if (!rc && (phase == 1 || phase == 3))
-        rc = psgd_orthogonalize_phase(it, use16, r, st);
+        rc = psgd_orthogonalize_phase(it, use16, r, phase == 3 ? &left : nullptr, st);
     if (!rc && (phase == 2 || phase == 3))
         rc = psgd_decompress_phase(it, use16, r, st);
     if (rc)

@@ -21,6 +21,9 @@ struct Req {
     uint16_t *Qt16;      // [KP, ldq] bf16 (Q^T), or nullptr
     int64_t ldq;         // a multiple of 8
     bool write32;        // store Q over Y
+    float *out;          // store the first nout columns of Q here (row stride ldo) instead, or nullptr
+    int64_t ldo;
+    int nout;
     int *stamp;          // status words of a workspace to stamp (stamp_subspace), or nullptr
 };
 
