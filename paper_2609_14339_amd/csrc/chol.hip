@@ -32,6 +32,8 @@ constexpr int kMaxJobs = 16;
 struct Job {
     double *G;
     float *T;
+    const double *part;
+    int blocks;
 };
 struct Batch {
     int count;
@@ -192,34 +194,49 @@ __device__ __forceinline__ void trail_update(double *S, int bi, int bj, int p, i
     st_d(A, acc, l);
 }
 
-template <bool INVERT>
+template <bool INVERT, bool PARTS>
 __global__ __launch_bounds__(1024) void chol_blocked_kernel(const Batch jb, int k, int KP)
 {
     extern __shared__ double S[];
-    __shared__ double sh_thresh;
     const Job &J = jb.j[blockIdx.z];
     double *G = J.G;
     const int NB = KP / kNB;
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // the lower blocks of G (zero outside the leading k x k)
+    // the lower blocks of G (zero outside the leading k x k); of partials only
+    // the upper blocks exist, so a block below the diagonal is read transposed
     for (int idx = tid; idx < KP * KP; idx += 1024) {
         const int i = idx / KP, c = idx - i * KP;
-        if ((c >> 4) <= (i >> 4))
-            S[bidx(i >> 4, c >> 4) * kBlk + eoff(i & 15, c & 15)] = (i < k && c < k) ? G[idx] : 0.0;
+        if ((c >> 4) <= (i >> 4)) {
+            double v = 0.0;
+            if (i < k && c < k) {
+                if constexpr (PARTS) {
+                    const int64_t kk = static_cast<int64_t>(KP) * KP;
+                    const double *p = J.part + ((c >> 4) == (i >> 4) ? idx : c * KP + i);
+#pragma unroll 8
+                    for (int b = 0; b < J.blocks; ++b)
+                        v += p[b * kk];
+                } else {
+                    v = G[idx];
+                }
+            }
+            S[bidx(i >> 4, c >> 4) * kBlk + eoff(i & 15, c & 15)] = v;
+        }
     }
+    if (PARTS)
+        __syncthreads();
+    double thresh = 0.0;   // wave 0 factors every diagonal block
     if (w == 0) {
         double mx = 0.0;
         for (int i = l; i < k; i += 64)
-            mx = fmax(mx, G[static_cast<int64_t>(i) * KP + i]);
+            mx = fmax(mx, PARTS ? S[bidx(i >> 4, i >> 4) * kBlk + eoff(i & 15, i & 15)]
+                                : G[static_cast<int64_t>(i) * KP + i]);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
             mx = fmax(mx, __shfl_xor(mx, off, 64));
-        if (l == 0)
-            sh_thresh = 1e-15 * k * mx;
+        thresh = 1e-15 * k * mx;
     }
     __syncthreads();
-    const double thresh = sh_thresh;
     double *Lg = INVERT ? nullptr : G;
     if (w == 0)
         factor_diag(S, thresh, Lg, KP);
@@ -326,10 +343,10 @@ int prepare(int KP)
 {
     if (!supported(KP))
         return set_error(ACSC_EINVAL, "chol: padded order %d not handled", KP);
-    int rc = allow_lds(chol_blocked_kernel<true>, lds_bytes(KP));
-    if (rc)
-        return rc;
-    return allow_lds(chol_blocked_kernel<false>, lds_bytes(KP));
+    int rc = allow_lds(chol_blocked_kernel<true, false>, lds_bytes(KP));
+    rc = rc ? rc : allow_lds(chol_blocked_kernel<true, true>, lds_bytes(KP));
+    rc = rc ? rc : allow_lds(chol_blocked_kernel<false, false>, lds_bytes(KP));
+    return rc ? rc : allow_lds(chol_blocked_kernel<false, true>, lds_bytes(KP));
 }
 
 int run(const char *tag, const std::vector<Req> &reqs, int k, int KP, bool invert, hipStream_t st)
@@ -340,12 +357,18 @@ int run(const char *tag, const std::vector<Req> &reqs, int k, int KP, bool inver
         Batch b{};
         b.count = static_cast<int>(std::min<size_t>(kMaxJobs, reqs.size() - c0));
         for (int i = 0; i < b.count; ++i)
-            b.j[i] = Job{reqs[c0 + i].G, reqs[c0 + i].T};
-        if (invert)
-            ACSC_LAUNCH(tag, chol_blocked_kernel<true>, dim3(1, 1, b.count), dim3(1024), lds_bytes(KP), st, b, k, KP);
+            b.j[i] = Job{reqs[c0 + i].G, reqs[c0 + i].T, reqs[c0 + i].part, reqs[c0 + i].blocks};
+        // a batch has partials for all of its matrices or for none
+        const bool parts = b.j[0].blocks > 0;
+        const dim3 grid(1, 1, b.count), block(1024);
+        if (invert && parts)
+            ACSC_LAUNCH(tag, (chol_blocked_kernel<true, true>), grid, block, lds_bytes(KP), st, b, k, KP);
+        else if (invert)
+            ACSC_LAUNCH(tag, (chol_blocked_kernel<true, false>), grid, block, lds_bytes(KP), st, b, k, KP);
+        else if (parts)
+            ACSC_LAUNCH(tag, (chol_blocked_kernel<false, true>), grid, block, lds_bytes(KP), st, b, k, KP);
         else
-            ACSC_LAUNCH(tag, chol_blocked_kernel<false>, dim3(1, 1, b.count), dim3(1024), lds_bytes(KP), st, b, k,
-                        KP);
+            ACSC_LAUNCH(tag, (chol_blocked_kernel<false, false>), grid, block, lds_bytes(KP), st, b, k, KP);
     }
     return ACSC_OK;
 }

@@ -360,10 +360,12 @@ struct SegBatch {
 // the MFMA's power draw, not HBM, sets their pace: covering 144 columns with
 // 16-wide tiles (rather than padding to 160 for 32x32 tiles) takes 8% less
 // time, and needs fewer fragment reads than 32x32 tiles plus a 16-wide one.
-// Up to 64 columns two workgroups share a CU, with two stages each: the same
+// Up to 48 columns two workgroups share a CU, with two stages each: the same
 // bytes in flight per CU, but one workgroup's start, end and barriers hide
-// under the other's stream.
-constexpr int kTwoPerCuNP = 64;
+// under the other's stream.  At 64 columns both forms stream alike (60 us
+// over an 8B-class layer's gradients), and one workgroup per CU leaves fewer
+// partials to add (5.5 against 8.1 us).
+constexpr int kTwoPerCuNP = 48;
 constexpr int waves_per_simd(int NT) { return NT * 16 <= kTwoPerCuNP ? 4 : 2; }
 
 template <bool TRANS, int NT, int S>

@@ -1580,7 +1580,9 @@ void gram_launch(int nt, bool parts, const std::vector<GramJob> &gj, dim3 grid, 
 
 // Gram matrices (fp64) of the first KP columns of one block per matrix.
 // `splits`: the partials (in pw.part) that each block still lies in, or 1.
-void gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::vector<int> &rows,
+// Returns the partials per matrix that are left for the factorisation to add
+// (few: see chol::kMaxPartials), or zeros with pw.gram formed.
+std::vector<int> gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::vector<int> &rows,
           const std::vector<int> &splits, hipStream_t st)
 {
     const int KP = ms[0].D.KP;
@@ -1619,8 +1621,17 @@ void gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::
         if (splits[i] <= 1)
             gj[i].src = A[i];   // a whole product among cut ones: one "partial", added to nothing
     gram_launch(nt, parts, gj, dim3(gy), KP, st);
+    std::vector<int> left;
+    int most = 0;
+    for (const GramJob &j : gj) {
+        left.push_back(j.blocks);
+        most = std::max(most, j.blocks);
+    }
+    if (most <= chol::kMaxPartials)
+        return left;
     launch_jobs("sc_gram_reduce", gram_reduce_kernel, rj, dim3(static_cast<unsigned>(cdiv(int64_t(KP) * KP, 32))),
                 dim3(256), 0, st, KP);
+    return std::vector<int>(ms.size(), 0);
 }
 
 // Q <- Y L^{-T}, `passes` times (CholeskyQR; two passes = CholeskyQR2), for
@@ -1643,11 +1654,11 @@ int orthonormalise(std::vector<Mat> &ms, bool onY, int passes, bool use16, std::
         rows.push_back(onY ? m.D.m : m.D.n);
     }
     for (int pass = 0; pass < passes; ++pass) {
-        gram(ms, A, rows, splits, st);
+        const std::vector<int> left = gram(ms, A, rows, splits, st);
         splits.assign(ms.size(), 1);   // added up by the Gram kernel
         std::vector<chol::Req> cj;
-        for (auto &m : ms)
-            cj.push_back(chol::Req{m.pw.gram, m.pw.T});
+        for (size_t i = 0; i < ms.size(); ++i)
+            cj.push_back(chol::Req{ms[i].pw.gram, ms[i].pw.T, ms[i].pw.gpart, left[i]});
         if (int rc = chol::run("sc_chol_inv", cj, d0.k, d0.KP, true, st))
             return rc;
         // fp32 Q is read by the second Gram of CholeskyQR2 and by the final
@@ -1792,10 +1803,11 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         for (auto &m : ms) {
             A.push_back(m.pw.Z);
             rows.push_back(m.D.n);
-            cj.push_back(chol::Req{m.pw.gram, nullptr});
             jj.push_back(JacJob{m.pw.gram, m.pw.Bu, m.pw.Bv, m.in->s, m.in->d, m.pw.info});
         }
-        gram(ms, A, rows, splits, st);
+        const std::vector<int> left = gram(ms, A, rows, splits, st);
+        for (size_t i = 0; i < ms.size(); ++i)
+            cj.push_back(chol::Req{ms[i].pw.gram, nullptr, ms[i].pw.gpart, left[i]});
         if ((rc = chol::run("sc_chol", cj, k, KP, false, st)))
             return rc;
         // the sweep cap can be lowered (not raised) through the environment, so

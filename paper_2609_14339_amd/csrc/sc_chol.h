@@ -23,7 +23,16 @@ namespace chol {
 struct Req {
     double *G;   // [KP, KP] fp64, row stride KP
     float *T;    // [KP, KP] fp32 (invert) or unused
+    // blocks > 0: G is not formed yet; its upper 16 x 16 blocks (the diagonal's
+    // whole) are the sums of that many partials, KP * KP apart
+    const double *part;
+    int blocks;
 };
+
+// Most partials per matrix that run() adds up while it loads: up to here the
+// one workgroup that factors a matrix reads them in the time that a launch
+// to add them costs (2.7 to 5 us), beyond it does not.
+constexpr int kMaxPartials = 16;
 
 // KP = padded order this kernel handles (a multiple of 16, at most SC_KMAX).
 bool supported(int KP);
