@@ -579,6 +579,7 @@ __device__ __forceinline__ void jacobi_finish(const JacJob &J, const T *A, int k
         for (int c2 = 0; c2 < k; ++c2)
             rk += (sig[c2] > sig[c]) || (sig[c2] == sig[c] && c2 < c);
         rank_of[c] = rk;
+        col_of[c] = c;   // a factor with NaNs has equal ranks and leaves places of col_of unset below
     }
     __syncthreads();
     // numerical rank: singular values at the fp32 rounding floor of the

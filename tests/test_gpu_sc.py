@@ -432,6 +432,24 @@ def test_ritz_step_at_every_block_count(pk, k):
         assert np.max(np.abs(B.T @ B - np.eye(k))) <= tol
 
 
+@pytest.mark.parametrize("dtype,r", [(torch.float32, 8), (torch.bfloat16, 40), (torch.bfloat16, 130)])
+def test_a_nan_gradient_leaves_the_next_build_alone(pk, dtype, r):
+    """A NaN in the anchor gradient spreads into its own prior only: the call
+    returns, and the same workspace then builds a clean matrix's prior to the
+    bits that a fresh one gives."""
+    m, n = 300, 400
+    g = workloads.gaussian((m, n), seed=2, dtype=dtype).cuda()
+    bad = g.clone()
+    bad[17, 23] = float("nan")
+    ws = pk.workspace(m, n, r, 16, dtype)
+    U, s, V, d = pk.sc_build_prior(bad, torch.zeros(m, n, device="cuda"), r, 0.9, 1e-3, 16, 2, seed=3, ws=ws)
+    again = pk.sc_build_prior(g, torch.zeros(m, n, device="cuda"), r, 0.9, 1e-3, 16, 2, seed=3, ws=ws)
+    fresh = pk.sc_build_prior(g, torch.zeros(m, n, device="cuda"), r, 0.9, 1e-3, 16, 2, seed=3)
+    torch.cuda.synchronize()
+    for x, y in zip(again, fresh):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
 @pytest.mark.parametrize("r,p", [(16, 8), (130, 16)])
 def test_build_status_reports_a_sweep_cap_and_a_missing_subspace_phase(pk, r, p, monkeypatch):
     """The Rayleigh-Ritz Jacobi (fp64 for k <= 128, fp32 above) reports its
