@@ -315,9 +315,12 @@ int sc_build_prior_batched(int count, const sc_matrix *mats, acsc_dtype dt, floa
  * call must follow the subspace call with the same arguments and
  * workspaces, in stream order, with nothing writing those workspaces in
  * between.  The ritz call reads neither G_anc nor beta, power_iters or seed.
- * The pair enqueues the same kernels in the same order as one
- * sc_build_prior_batched call, so the results are bit-identical.  Errors as
- * for sc_build_prior_batched. */
+ * It may take the matrices of one subspace call in several calls, or those
+ * of several in one: the hand-over is each matrix's own.  With the same
+ * matrices in the same order the pair adds the same sums in the same order
+ * as one sc_build_prior_batched call, so the results are bit-identical; in
+ * other batches the Gram matrix's fp64 sums may be grouped differently.
+ * Errors as for sc_build_prior_batched. */
 int sc_build_subspace_batched(int count, const sc_matrix *mats, acsc_dtype dt, float beta, int r,
                               int oversample, int power_iters, float tau, uint64_t seed,
                               hipStream_t stream);

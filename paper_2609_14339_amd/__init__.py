@@ -451,7 +451,7 @@ def sc_build_ritz_batched(items, r: int, beta: float, tau: float, oversample: in
                           stream=None):
     """Second phase of sc_build_prior_batched (Rayleigh-Ritz on Z: U, s, V, d);
     the same arguments and workspaces as the sc_build_subspace_batched call
-    it follows."""
+    it follows, whose matrices may come in several such calls."""
     _build_batched(lib.sc_build_ritz_batched, items, r, beta, tau, oversample, power_iters, seed, dtype, stream)
 
 

@@ -448,8 +448,6 @@ void launch_blend(const char *tag, const std::vector<BlendReq> &reqs, int RP, fl
 
 }  // namespace
 
-std::vector<int> plan_splits(const std::vector<PassReq> &reqs) { return plan(reqs).splits; }
-
 int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStream_t st, int *splits)
 {
     if (reqs.empty())

@@ -1202,23 +1202,7 @@ std::vector<size_t> longest_first(const std::vector<Req> &reqs)
     return order;
 }
 
-}  // namespace
-
-void add_partials(const std::vector<Partials> &red, hipStream_t st)
-{
-    for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
-        RedBatch b{};
-        b.count = static_cast<int>(std::min<size_t>(kMaxJobs, red.size() - c0));
-        int64_t tot = 1;
-        for (int i = 0; i < b.count; ++i) {
-            b.j[i] = red[c0 + i];
-            tot = std::max<int64_t>(tot, static_cast<int64_t>(b.j[i].M) * (b.j[i].NP / 4));
-        }
-        const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(tot, 256), 8192));
-        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
-    }
-}
-
+// The k pieces that each request is cut into (a function of the batch's shapes).
 std::vector<int> plan_splits(const std::vector<Req> &reqs)
 {
     std::vector<int> out(reqs.size(), 1);
@@ -1240,6 +1224,23 @@ std::vector<int> plan_splits(const std::vector<Req> &reqs)
             out[at[i]] = sp[i];
     }
     return out;
+}
+
+}  // namespace
+
+void add_partials(const std::vector<Partials> &red, hipStream_t st)
+{
+    for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
+        RedBatch b{};
+        b.count = static_cast<int>(std::min<size_t>(kMaxJobs, red.size() - c0));
+        int64_t tot = 1;
+        for (int i = 0; i < b.count; ++i) {
+            b.j[i] = red[c0 + i];
+            tot = std::max<int64_t>(tot, static_cast<int64_t>(b.j[i].M) * (b.j[i].NP / 4));
+        }
+        const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(tot, 256), 8192));
+        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
+    }
 }
 
 int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits_out)

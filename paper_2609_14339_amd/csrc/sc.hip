@@ -1766,10 +1766,10 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         return q;
     };
     std::vector<int> splits(ms.size(), 1);
-    auto pass = [&](bool mz) {
-        if (use16)
-            return pass::run(mz ? "sc_pass_mz" : "sc_pass_mtq", !mz, reqs16(mz), st, splits.data());
-        return f32::pass(mz ? "sc_pass_mz" : "sc_pass_mtq", !mz, reqs32(mz), st, splits.data());
+    auto pass = [&](bool mz, bool whole = false) {
+        const char *tag = mz ? "sc_pass_mz" : "sc_pass_mtq";
+        int *left = whole ? nullptr : splits.data();
+        return use16 ? pass::run(tag, !mz, reqs16(mz), st, left) : f32::pass(tag, !mz, reqs32(mz), st, left);
     };
     int rc = ACSC_OK;
     if (phases & kPhaseSubspace) {
@@ -1789,7 +1789,10 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
                 return rc;
         }
         // Z = M^T Q (= B^T) for the Rayleigh-Ritz step: B B^T = Z^T Z = L L^T, SVD of L by Jacobi.
-        if ((rc = pass(false)))
+        // A subspace call of its own leaves Z whole: how a product is cut
+        // depends on its batch, and the Rayleigh-Ritz call may come in another one.
+        const bool whole = !(phases & kPhaseRitz);
+        if ((rc = pass(false, whole)))
             return rc;
     }
     if (!(phases & kPhaseRitz))
@@ -1799,8 +1802,6 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
         std::vector<int> rows;
         std::vector<chol::Req> cj;
         std::vector<JacJob> jj;
-        // the last product of the subspace phase lies in the partials of its plan
-        splits = use16 ? pass::plan_splits(reqs16(false)) : f32::plan_splits(reqs32(false));
         for (auto &m : ms) {
             A.push_back(m.pw.Z);
             rows.push_back(m.D.n);

@@ -28,9 +28,6 @@ struct PassReq {
     int cap;
 };
 
-// The k pieces that pass() cuts each request into (a function of the shapes).
-std::vector<int> plan_splits(const std::vector<PassReq> &reqs);
-
 // Enqueue the products (one NP per call).  With `splits` a product that was
 // cut along k is left in its partials (stride M * NP, row stride NP), as by
 // pass::run; without it C always holds the product.

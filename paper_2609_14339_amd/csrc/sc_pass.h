@@ -58,9 +58,6 @@ struct Partials {
 };
 void add_partials(const std::vector<Partials> &red, hipStream_t st);
 
-// The k pieces that run() cuts each request into (a function of the shapes).
-std::vector<int> plan_splits(const std::vector<Req> &reqs);
-
 // Enqueue one pass per request (all requests share NP) on `st`.  With
 // `splits` (one entry per request) a product that was cut along k is left as
 // that many partials (partial p at part + p * M * NP, row stride NP) for the

@@ -405,6 +405,41 @@ def test_build_in_two_phases_equals_one_call(pk, fused, dtype):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_ritz_phase_takes_the_matrices_of_a_subspace_call_one_by_one(pk, dtype):
+    """One subspace call on a batch whose last products are cut along k as the
+    batch asks for (8, 1, 1 pieces in bf16; alone these matrices would be cut
+    in 16, 2, 2), then a ritz call per matrix: each gives the prior that one
+    call on the batch gives.  Only the fp64 Gram sums may be grouped
+    differently (1e-16), so the fp32 outputs agree to a few rounding errors:
+    1e-6 on the singular values, 1e-5 on U diag(s) V^T."""
+    shapes, r, p = [(8192, 256), (1024, 16384), (1024, 16384)], 64, 16
+    runs = []
+    for split in (False, True):
+        items = []
+        for i, (m, n) in enumerate(shapes):
+            gp = workloads.grad_pair(workloads.GradSpec(((m, n),), r, (1.0, 100.0), (r,), dtype, None, None), 9, i, 0,
+                                     "cpu")
+            outs = tuple(torch.zeros(*s, device="cuda") for s in ((m, r), (r,), (n, r), (r,)))
+            items.append(dict(G_anc=gp.G_anc.cuda(), M=torch.zeros(m, n, device="cuda"), out=outs,
+                              ws=pk.workspace(m, n, r, p, dtype)))
+        args = (r, workloads.BETA, workloads.TAU, p, 2)
+        if split:
+            pk.sc_build_subspace_batched(items, *args, seed=70, dtype=dtype)
+            for it in items:
+                pk.sc_build_ritz_batched([it], *args, seed=70, dtype=dtype)
+        else:
+            pk.sc_build_prior_batched(items, *args, seed=70, dtype=dtype)
+        torch.cuda.synchronize()
+        pk.sc_build_status([it["ws"] for it in items])
+        runs.append(items)
+    for a, b in zip(*runs):
+        (U0, s0, V0, _), (U1, s1, V1, _) = a["out"], b["out"]
+        assert (s1 / s0 - 1).abs().max().item() <= 1e-6
+        P0 = (U0 * s0) @ V0.t()
+        assert ((U1 * s1) @ V1.t() - P0).norm().item() <= 1e-5 * P0.norm().item()
+
+
 @pytest.mark.parametrize("k", [1, 3, 5, 8, 9, 16, 17, 31, 44, 61, 80, 100, 113, 128, 129, 160, 161, 189])
 def test_ritz_step_at_every_block_count(pk, k):
     """The Jacobi works on blocks of four columns (odd block counts and partial
