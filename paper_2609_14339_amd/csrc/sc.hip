@@ -1188,6 +1188,7 @@ struct SumJob {
     const void *G;
     int64_t count;    // elements of G (contiguous)
     int vec;          // 16-byte aligned G: 16-byte loads but for the last elements
+    int chunk32;      // whole 16-byte chunks only: a chunk's squares are added in fp32
     double *part;     // [kSumBlocks]
 };
 
@@ -1216,18 +1217,27 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const Batch<SumJob> jb)
     const int64_t stride = static_cast<int64_t>(kSumBlocks) * 256;
     const int64_t start = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (J.vec) {
-        // squares of bf16 are exact in fp32; the V of one chunk are added in fp32
+        // squares of bf16 are exact in fp32; with chunk32 the V of one chunk are
+        // added in fp32, otherwise every square is formed and added in fp64
         for (int64_t c = start; c < J.count / V; c += stride) {
             const uint4 raw = reinterpret_cast<const uint4 *>(G)[c];
             GT e[V];
             __builtin_memcpy(e, &raw, sizeof(e));
-            float s = 0.f;
+            if (J.chunk32) {
+                float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < V; ++i) {
-                const float g = to_f32<GT>(e[i]);
-                s += g * g;
+                for (int i = 0; i < V; ++i) {
+                    const float g = to_f32<GT>(e[i]);
+                    s += g * g;
+                }
+                acc += s;
+            } else {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    const double g = to_f32<GT>(e[i]);
+                    acc += g * g;
+                }
             }
-            acc += s;
         }
         const int64_t i = J.count / V * V + start;
         if (i < J.count) {
@@ -1841,8 +1851,8 @@ void clip_norm(const std::vector<Mat> &ms, int r, float alpha, const AdamCtx &ad
     std::vector<SumJob> sj;
     for (const Mat &m : ms) {
         const int64_t cnt = static_cast<int64_t>(m.D.m) * m.D.n;
-        const bool vec = aligned(m.in->G, 16);
-        sj.push_back(SumJob{m.in->G, cnt, vec ? 1 : 0, m.cw.sq});
+        sj.push_back(SumJob{m.in->G, cnt, aligned(m.in->G, 16) ? 1 : 0,
+                            cnt % static_cast<int64_t>(16 / sizeof(GT)) == 0 ? 1 : 0, m.cw.sq});
     }
     launch_jobs("sc_sumsq", sumsq_kernel<GT>, sj, dim3(kSumBlocks), dim3(256), 0, st);
     for (size_t c0 = 0; c0 < ms.size(); c0 += kMaxBatch) {

@@ -131,6 +131,24 @@ def test_bf16_streamed_tile_kernel(pk, m, n, r, misalign):
     _compare(cases, got, ref, 2e-2)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m,n", [(301, 403), (211, 571), (66, 1027)])
+def test_norm_of_a_count_that_fills_no_whole_chunk_is_summed_in_fp64(pk, m, n, dtype):
+    """Every 16 bytes of G hold a one and then values whose squares are just
+    below half an ulp of one, which fp32 adds would drop (up to 2e-7 of the
+    norm); m n is no multiple of their number.  With alpha = 1 the norm is
+    ||G||: the fp64 sum (error about 1e-12) rounded to fp32."""
+    V = 8 if dtype == torch.bfloat16 else 4
+    assert m * n % V != 0
+    g = torch.full((m * n,), 255 / 256 * 2.0 ** -12, dtype=torch.float64)
+    g[::V] = 1.0
+    G = g.view(m, n).to(dtype)
+    assert torch.equal(G.double(), g.view(m, n))
+    c = dict(_case(m, n, 8, 3, dtype, 5), G=G)
+    _, norm = _run(pk, [c], 8, 1.0, 5, 1.0, dtype)
+    assert np.float32(norm) == np.float32(g.square().sum().sqrt().item())
+
+
 def test_norm_spans_more_than_one_launch(pk):
     # 18 matrices: two launches of the norm kernel accumulate one global norm
     cases = [_case(64 + 8 * i, 96, 8, 40 + i, torch.bfloat16, 3) for i in range(18)]
