@@ -360,17 +360,11 @@ struct SegBatch {
 // the MFMA's power draw, not HBM, sets their pace: covering 144 columns with
 // 16-wide tiles (rather than padding to 160 for 32x32 tiles) takes 8% less
 // time, and needs fewer fragment reads than 32x32 tiles plus a 16-wide one.
-// Up to 48 columns two workgroups share a CU, with two stages each: the same
-// bytes in flight per CU, but one workgroup's start, end and barriers hide
-// under the other's stream.  At 64 columns both forms stream alike (60 us
-// over an 8B-class layer's gradients), and one workgroup per CU leaves fewer
-// partials to add (5.5 against 8.1 us).
-constexpr int kTwoPerCuNP = 48;
-constexpr int waves_per_simd(int NT) { return NT * 16 <= kTwoPerCuNP ? 4 : 2; }
-
-template <bool TRANS, int NT, int S>
-__global__ __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT), waves_per_simd(NT)))) void pass_dma_kernel(const SegBatch sb, int np)
+// One workgroup per CU with three stages, or, for the launches that two_per_cu()
+// names, two with two stages each (W: waves per SIMD).
+template <bool TRANS, int NT, int S, int W>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W, W))) void pass_dma_kernel(const SegBatch sb,
+                                                                                                  int np)
 {
     const int wg = static_cast<int>(blockIdx.x);
     int si = 0;
@@ -648,39 +642,48 @@ void launch_unaligned(const char *tag, const std::vector<Job> &jobs, int gx, int
     }
 }
 
+// Widest thin factor that leaves LDS and registers for two workgroups per CU.
+constexpr int kTwoPerCuNP = 48;
+
 template <bool TRANS, int NTK>
-void launch_segs(const char *tag, const SegBatch &b, int grid, int np, hipStream_t st)
+void launch_segs(const char *tag, const SegBatch &b, int grid, int np, int per_cu, hipStream_t st)
 {
-    // two workgroups per CU with two LDS stages each; else three stages while
-    // they fit in 160 KiB, else two
-    constexpr int S = NTK * 16 > kTwoPerCuNP && 3 * (256 * 128 + NTK * 16 * 128) <= 160 * 1024 ? 3 : 2;
-    auto kern = pass_dma_kernel<TRANS, NTK, S>;
+    if constexpr (NTK * 16 <= kTwoPerCuNP) {
+        if (per_cu == 2) {
+            auto kern = pass_dma_kernel<TRANS, NTK, 2, 4>;
+            ACSC_LAUNCH(tag, kern, dim3(grid), dim3(512), 0, st, b, np);
+            return;
+        }
+    }
+    // three LDS stages while they fit in 160 KiB, else two
+    constexpr int S = (3 * (256 * 128 + NTK * 16 * 128) <= 160 * 1024) ? 3 : 2;
+    auto kern = pass_dma_kernel<TRANS, NTK, S, 2>;
     ACSC_LAUNCH(tag, kern, dim3(grid), dim3(512), 0, st, b, np);
 }
 
 template <bool TRANS>
-void launch_dma(const char *tag, const SegBatch &b, int grid, int np, hipStream_t st)
+void launch_dma(const char *tag, const SegBatch &b, int grid, int np, int per_cu, hipStream_t st)
 {
     switch (np / 16) {
-    case 1: launch_segs<TRANS, 1>(tag, b, grid, np, st); break;
-    case 2: launch_segs<TRANS, 2>(tag, b, grid, np, st); break;
-    case 3: launch_segs<TRANS, 3>(tag, b, grid, np, st); break;
-    case 4: launch_segs<TRANS, 4>(tag, b, grid, np, st); break;
-    case 5: launch_segs<TRANS, 5>(tag, b, grid, np, st); break;
-    case 6: launch_segs<TRANS, 6>(tag, b, grid, np, st); break;
-    case 7: launch_segs<TRANS, 7>(tag, b, grid, np, st); break;
-    case 8: launch_segs<TRANS, 8>(tag, b, grid, np, st); break;
-    case 9: launch_segs<TRANS, 9>(tag, b, grid, np, st); break;
-    case 10: launch_segs<TRANS, 10>(tag, b, grid, np, st); break;
-    case 11: launch_segs<TRANS, 11>(tag, b, grid, np, st); break;
-    default: launch_segs<TRANS, 12>(tag, b, grid, np, st); break;
+    case 1: launch_segs<TRANS, 1>(tag, b, grid, np, per_cu, st); break;
+    case 2: launch_segs<TRANS, 2>(tag, b, grid, np, per_cu, st); break;
+    case 3: launch_segs<TRANS, 3>(tag, b, grid, np, per_cu, st); break;
+    case 4: launch_segs<TRANS, 4>(tag, b, grid, np, per_cu, st); break;
+    case 5: launch_segs<TRANS, 5>(tag, b, grid, np, per_cu, st); break;
+    case 6: launch_segs<TRANS, 6>(tag, b, grid, np, per_cu, st); break;
+    case 7: launch_segs<TRANS, 7>(tag, b, grid, np, per_cu, st); break;
+    case 8: launch_segs<TRANS, 8>(tag, b, grid, np, per_cu, st); break;
+    case 9: launch_segs<TRANS, 9>(tag, b, grid, np, per_cu, st); break;
+    case 10: launch_segs<TRANS, 10>(tag, b, grid, np, per_cu, st); break;
+    case 11: launch_segs<TRANS, 11>(tag, b, grid, np, per_cu, st); break;
+    default: launch_segs<TRANS, 12>(tag, b, grid, np, per_cu, st); break;
     }
 }
 
 // ---------------------------------------------------------------------------
 // Workgroup order of the DMA passes.  Workgroups go to the XCDs in turn
 // (workgroup i to XCD i % X) and, within an XCD, to whichever CU frees up
-// first; one pass workgroup fills a CU.  A batch that mixes long and short
+// first (per_cu workgroups at a time).  A batch that mixes long and short
 // rows (the 70B-class build: 128 row blocks of 448 steps, 576 of 128) then
 // ends with a round in which only some CUs work.  The plan below simulates
 // that dispatch and, where it shortens the simulated makespan, moves the
@@ -756,12 +759,36 @@ void device_cus(int &xcds, int &cus_per_xcd)
     cus_per_xcd = std::max(1, cus / xcds);
 }
 
-// The plan depends only on the batch's shapes and the device, so it is made
-// once per distinct batch and kept.
-SegPlan plan(const std::vector<JobShape> &js)
+// Whether a launch of narrow passes takes two workgroups per CU.  They keep as
+// many bytes in flight per CU as one, with a stage less each, and their starts,
+// ends and barriers hide under each other; alone on its CU a workgroup is
+// faster with three stages.  So two are for a launch of more workgroups than
+// CUs (four 9000 x 9000 by 48, cut in 288: 131 us, against 153 for one per CU
+// over whole rows; 70400 x 8192 by 32, 275 whole row blocks: 209 against 254),
+// unless they are whole row blocks that fill a second round of one per CU as
+// well (equal from 460 on).  With no more workgroups than CUs, one: 26 us
+// against 31 over 8192 x 8192 by 16, 92 against 100 over eight 8192 x 4096 by 32.
+bool two_per_cu(const std::vector<JobShape> &js, int np)
 {
     int xcds = 8, cpx = 32;
     device_cus(xcds, cpx);
+    const int64_t cus = static_cast<int64_t>(xcds) * cpx;
+    int64_t wgs = 0;
+    bool whole = true;
+    for (const JobShape &j : js) {
+        wgs += static_cast<int64_t>(j.nrb) * j.splits;
+        whole = whole && j.splits == 1;
+    }
+    return np <= kTwoPerCuNP && wgs > cus && !(whole && 5 * wgs > 9 * cus);
+}
+
+// The plan depends only on the batch's shapes and the device, so it is made
+// once per distinct batch and kept.
+SegPlan plan(const std::vector<JobShape> &js, int per_cu)
+{
+    int xcds = 8, cpx = 32;
+    device_cus(xcds, cpx);
+    cpx *= per_cu;
     std::vector<int64_t> key{xcds, cpx};
     for (const JobShape &j : js)
         key.insert(key.end(), {j.nrb, j.splits, j.kchunk, j.K, j.halvable ? 1 : 0});
@@ -1101,7 +1128,7 @@ void ema_launch(const char *tag, const EmaBatch &b, int grid, int np, float a, f
 }
 
 // k pieces per row block for a batch whose row blocks do not fill the GPU.
-// One pass workgroup fills a CU, so the pass takes as long as the CU with the
+// A CU takes one pass workgroup (narrow ones: up to two), so the pass takes as long as the CU with the
 // most steps: a common piece length serves a batch that mixes row lengths
 // better than one split count for every job (with 2048- and 8192-deep rows
 // cut in four, the CUs of the long rows work four times as long as the
@@ -1303,14 +1330,15 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
             js.push_back(JobShape{static_cast<int>(cdiv(q.M, kBM)), vsplits[c0 + i], vchunk[c0 + i], q.K,
                                   q.part != nullptr && max_splits(q.M, q.K) >= 2 && q.K >= 2 * kBK});
         }
-        const SegPlan pl = plan(js);
+        const int per_cu = two_per_cu(js, NP) ? 2 : 1;
+        const SegPlan pl = plan(js, per_cu);
         b.nseg = static_cast<int>(pl.segs.size());
         for (size_t i = 0; i < pl.segs.size(); ++i)
             b.s[i] = pl.segs[i];
         if (trans)
-            launch_dma<true>(tag, b, pl.grid, NP, st);
+            launch_dma<true>(tag, b, pl.grid, NP, per_cu, st);
         else
-            launch_dma<false>(tag, b, pl.grid, NP, st);
+            launch_dma<false>(tag, b, pl.grid, NP, per_cu, st);
         for (size_t i = 0; i < cnt; ++i) {
             const int h = pl.halved[i];
             if (h <= 0)
@@ -1367,7 +1395,7 @@ int ema_run(const char *tag, const std::vector<EmaReq> &reqs, float a, float b, 
             js.push_back(JobShape{static_cast<int>(cdiv(q.m, kBM)), 1, static_cast<int>(round_up(q.n, kBK)), q.n,
                                   q.part != nullptr && max_splits(q.m, q.n) >= 2 && q.n >= 2 * kBK});
         }
-        const SegPlan pl = plan(js);
+        const SegPlan pl = plan(js, 1);
         eb.nseg = static_cast<int>(pl.segs.size());
         for (size_t i = 0; i < pl.segs.size(); ++i)
             eb.s[i] = pl.segs[i];

@@ -115,6 +115,27 @@ def test_phases_equal_the_step_and_project_matches_oracle(pk, dtype):
             assert torch.equal(x[k], y[k]), k
 
 
+@pytest.mark.parametrize("m,n,count", [(4200, 3848, 9), (520, 4248, 16)])
+def test_second_projection_at_two_workgroups_per_cu(pk, m, n, count):
+    """Q' = M^T P_hat of batches whose row blocks (over n) fill just over half
+    the CUs (9 x 16, cut) or a second round badly (16 x 17, whole rows), which
+    take two workgroups per CU.  Against float64 from the library's own M and
+    P_hat, rounded to bf16 as the pass reads them: fp32 sums, 1e-5."""
+    r, dev = 20, "cuda"
+    g = torch.Generator(device=dev).manual_seed(n)
+    items, M = [], []
+    for _ in range(count):
+        G = torch.randn(m, n, generator=g, device=dev).bfloat16()
+        E = torch.randn(m, n, generator=g, device=dev) * 0.1
+        M.append((E + G.float()).bfloat16())
+        items.append(dict(G=G, E=E, P=torch.zeros(m, r, device=dev), Q=torch.randn(n, r, generator=g, device=dev),
+                          out=torch.zeros_like(G), ws=pk.psgd_workspace(m, n, r, torch.bfloat16)))
+    pk.psgd_step(items, r, torch.bfloat16)
+    for i, (it, Mi) in enumerate(zip(items, M)):
+        ref = Mi.double().t() @ it["P"].bfloat16().double()
+        assert (it["Q"].double() - ref).norm().item() <= 1e-5 * ref.norm().item(), i
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_steps_carry_memory_and_warm_start(pk, dtype):
     """Four steps on changing gradients: at every step the oracle takes the

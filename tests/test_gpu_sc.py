@@ -681,6 +681,29 @@ def test_fused_ema_pass_on_ragged_shapes(pk):
                 assert torch.equal(x, y), (arrival, i)
 
 
+@pytest.mark.parametrize("m,n,count", [(3848, 4200, 9), (4248, 520, 16)])
+def test_narrow_passes_at_two_workgroups_per_cu(pk, m, n, count):
+    """Batches of narrow passes whose row blocks fill just over half the CUs
+    (9 x 16 row blocks, cut) or a second round badly (16 x 17, whole rows)
+    take two workgroups per CU.  G_proj of every matrix against its float64
+    value: bf16 rounds G V's factor, U X_f and the output, 2^-9 each at most
+    (the transposed form is in the PowerSGD tests)."""
+    r, dev = 20, "cuda"
+    g = torch.Generator(device=dev).manual_seed(m)
+    items = []
+    for _ in range(count):
+        U, V = (torch.linalg.qr(torch.randn(s, r, generator=g, device=dev))[0].contiguous() for s in (m, n))
+        d = torch.rand(r, generator=g, device=dev)
+        G = (torch.randn(m, n, generator=g, device=dev) + 40 * (U @ V.t())).bfloat16()
+        items.append(dict(G=G, prior=(U, d, V), out=torch.zeros_like(G), ws=pk.workspace(m, n, r, 0, torch.bfloat16)))
+    pk.sc_correct_batched(items, r, workloads.ALPHA)
+    for i, it in enumerate(items):
+        U, d, V = (t.double() for t in it["prior"])
+        G = it["G"].double()
+        ref = workloads.ALPHA * G + (1 - workloads.ALPHA) * ((U * d) @ (U.t() @ (G @ V)) @ (V * d).t())
+        assert (it["out"].double() - ref).norm().item() <= 3 * 2.0 ** -9 * ref.norm().item(), i
+
+
 def test_stats_filter_times_only_the_named_kernel(pk):
     """acsc_stats_only: with a name set, only that kernel's launches are
     timed; the build's result does not depend on the timing."""
