@@ -204,23 +204,32 @@ __global__ __launch_bounds__(1024) void chol_blocked_kernel(const Batch jb, int 
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the lower blocks of G (zero outside the leading k x k); of partials only
-    // the upper blocks exist, so a block below the diagonal is read transposed
+    // the upper blocks exist: they are read along their rows, and a block
+    // beside the diagonal is turned on its way into LDS
     for (int idx = tid; idx < KP * KP; idx += 1024) {
         const int i = idx / KP, c = idx - i * KP;
-        if ((c >> 4) <= (i >> 4)) {
-            double v = 0.0;
-            if (i < k && c < k) {
-                if constexpr (PARTS) {
+        if constexpr (PARTS) {
+            if ((i >> 4) <= (c >> 4)) {
+                double v = 0.0;
+                if (i < k && c < k) {
                     const int64_t kk = static_cast<int64_t>(KP) * KP;
-                    const double *p = J.part + ((c >> 4) == (i >> 4) ? idx : c * KP + i);
-#pragma unroll 8
-                    for (int b = 0; b < J.blocks; ++b)
-                        v += p[b * kk];
-                } else {
-                    v = G[idx];
+                    const double *p = J.part + idx;
+                    // eight loads in flight; past the last partial, the last again as zero
+                    for (int b = 0; b < J.blocks; b += 8) {
+                        double x[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            x[e] = p[min(b + e, J.blocks - 1) * kk];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            v += b + e < J.blocks ? x[e] : 0.0;
+                    }
                 }
+                const int at = (i >> 4) == (c >> 4) ? eoff(i & 15, c & 15) : eoff(c & 15, i & 15);
+                S[bidx(c >> 4, i >> 4) * kBlk + at] = v;
             }
-            S[bidx(i >> 4, c >> 4) * kBlk + eoff(i & 15, c & 15)] = v;
+        } else if ((c >> 4) <= (i >> 4)) {
+            S[bidx(i >> 4, c >> 4) * kBlk + eoff(i & 15, c & 15)] = i < k && c < k ? G[idx] : 0.0;
         }
     }
     if (PARTS)

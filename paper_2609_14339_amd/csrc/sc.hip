@@ -1592,7 +1592,7 @@ void gram_launch(int nt, bool parts, const std::vector<GramJob> &gj, dim3 grid, 
 // Gram matrices (fp64) of the first KP columns of one block per matrix.
 // `splits`: the partials (in pw.part) that each block still lies in, or 1.
 // Returns the partials per matrix that are left for the factorisation to add
-// (few: see chol::kMaxPartials), or zeros with pw.gram formed.
+// (see chol::adds_partials), or zeros with pw.gram formed.
 std::vector<int> gram(const std::vector<Mat> &ms, const std::vector<float *> &A, const std::vector<int> &rows,
           const std::vector<int> &splits, hipStream_t st)
 {
@@ -1638,7 +1638,7 @@ std::vector<int> gram(const std::vector<Mat> &ms, const std::vector<float *> &A,
         left.push_back(j.blocks);
         most = std::max(most, j.blocks);
     }
-    if (most <= chol::kMaxPartials)
+    if (chol::adds_partials(KP, most))
         return left;
     launch_jobs("sc_gram_reduce", gram_reduce_kernel, rj, dim3(static_cast<unsigned>(cdiv(int64_t(KP) * KP, 32))),
                 dim3(256), 0, st, KP);

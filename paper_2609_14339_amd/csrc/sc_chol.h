@@ -29,10 +29,17 @@ struct Req {
     int blocks;
 };
 
-// Most partials per matrix that run() adds up while it loads: up to here the
-// one workgroup that factors a matrix reads them in the time that a launch
-// to add them costs (2.7 to 5 us), beyond it does not.
-constexpr int kMaxPartials = 16;
+// Whether run() adds up a matrix's partials while it loads.  The one workgroup
+// that factors it then reads blocks * KP^2 / 2 doubles, one chain of latencies
+// per 1024 elements of G; a launch that adds them first costs about 5 us.
+// Measured on a whole build, added here and by a launch: KP = 16, 16 partials
+// 187 and 195 us; KP = 32, 8 partials 248 and 255 (16: 260 both); KP = 48,
+// 8 partials 374 and 382, 12 partials 378 and 366; KP = 64, 4 partials 472
+// and 463; KP = 144, 16 partials 1709 and 1528.
+inline bool adds_partials(int KP, int blocks)
+{
+    return KP <= 48 && blocks <= 16 && blocks * KP * KP * 8 <= 144 * 1024;
+}
 
 // KP = padded order this kernel handles (a multiple of 16, at most SC_KMAX).
 bool supported(int KP);

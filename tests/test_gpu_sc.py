@@ -467,6 +467,32 @@ def test_ritz_step_at_every_block_count(pk, k):
         assert np.max(np.abs(B.T @ B - np.eye(k))) <= tol
 
 
+@pytest.mark.parametrize("n,k,added", [(16, 16, True), (40, 13, True), (100, 30, True), (256, 48, True),
+                                       (257, 48, False), (512, 17, True), (512, 32, True), (513, 32, False),
+                                       (64, 50, False), (500, 72, False), (512, 144, False)])
+def test_who_adds_the_gram_partials(pk, n, k, added):
+    """The factorisation adds up the Gram partials (one per 32 rows) of orders
+    up to 48 with up to 16 of them and 144 KiB, where that takes less time than the
+    launch that adds them otherwise.  An n x n matrix of rank k: U diag(s) V^T
+    is the matrix itself (fp32 products; the fp32 Jacobi beyond order 128
+    stops at 1e-5)."""
+    g = torch.Generator().manual_seed(k)
+    q1, q2 = (torch.linalg.qr(torch.randn(n, k, generator=g, dtype=torch.float64))[0] for _ in range(2))
+    G = ((q1 * torch.exp(torch.linspace(math.log(10.0), 0.0, k, dtype=torch.float64))) @ q2.T).float()
+    M = torch.zeros(n, n, device="cuda")
+    ws = pk.workspace(n, n, k, 0, torch.float32)
+    try:
+        pk.acsc_stats_enable(True)
+        U, s, V, d = pk.sc_build_prior(G.cuda(), M, k, 0.0, 0.0, 0, 1, seed=1, ws=ws)
+        torch.cuda.synchronize()
+        launches = pk.acsc_stats_read()
+    finally:
+        pk.acsc_stats_enable(False)
+    pk.sc_build_status([ws])
+    assert ("sc_gram_reduce" not in launches) == added
+    assert osp.rel_fro(_np(U) * _np(s) @ _np(V).T, G.double().numpy()) <= (2e-4 if k > 128 else 2e-5)
+
+
 @pytest.mark.parametrize("dtype,r", [(torch.float32, 8), (torch.bfloat16, 40), (torch.bfloat16, 130)])
 def test_a_nan_gradient_leaves_the_next_build_alone(pk, dtype, r):
     """A NaN in the anchor gradient spreads into its own prior only: the call
