@@ -42,6 +42,8 @@ METRIC = "mask pack/unpack GB/s + spectral-correction TFLOP/s, % of HBM/MFMA pea
 PEAK_HBM = 8000.0          # GB/s
 PEAK_BF16 = 2500.0         # TFLOP/s dense
 PEAK_F32 = 157.3           # TFLOP/s (fp32 matrix and vector)
+# the kernels of a correction (sc_correct_batched), by the library's timing names
+CORRECTION_KERNELS = ("sc_vconvert", "sc_gv", "sc_gv_reduce", "sc_utt", "sc_inner_reduce", "sc_ux", "sc_blend")
 
 
 def parse():
@@ -416,10 +418,9 @@ def main():
     # the method's cadence (Table 2: an anchor arrives every K = 20 fast
     # steps): every step masks and corrects, one step in 20 also builds the
     # prior; device time from the summed kernel times of each part
-    corr_tags = ("sc_vconvert", "sc_gv", "sc_utt", "sc_inner_reduce", "sc_filter", "sc_ux", "sc_blend")
     part_ms = {"masking": 0.0, "correction": 0.0, "build": 0.0}
     for name, (n, ms) in per_step.items():
-        part = "masking" if name.startswith("ac_") else "correction" if name in corr_tags else "build"
+        part = "masking" if name.startswith("ac_") else "correction" if name in CORRECTION_KERNELS else "build"
         part_ms[part] += ms
     staleness = 20
     cyc_ms = part_ms["masking"] + part_ms["correction"] + part_ms["build"] / staleness

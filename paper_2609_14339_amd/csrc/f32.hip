@@ -448,7 +448,8 @@ void launch_blend(const char *tag, const std::vector<BlendReq> &reqs, int RP, fl
 
 }  // namespace
 
-int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStream_t st, int *splits)
+int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStream_t st, int *splits,
+         const char *red_tag)
 {
     if (reqs.empty())
         return ACSC_OK;
@@ -482,7 +483,7 @@ int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStrea
         else
             launch<false>(tag, NP, p.rows > 16, b, gx, st);
     }
-    pass::add_partials(red, st);
+    pass::add_partials(red_tag, red, st);
     return ACSC_OK;
 }
 

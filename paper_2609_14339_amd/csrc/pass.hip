@@ -1255,7 +1255,7 @@ std::vector<int> plan_splits(const std::vector<Req> &reqs)
 
 }  // namespace
 
-void add_partials(const std::vector<Partials> &red, hipStream_t st)
+void add_partials(const char *tag, const std::vector<Partials> &red, hipStream_t st)
 {
     for (size_t c0 = 0; c0 < red.size(); c0 += kMaxJobs) {
         RedBatch b{};
@@ -1266,11 +1266,12 @@ void add_partials(const std::vector<Partials> &red, hipStream_t st)
             tot = std::max<int64_t>(tot, static_cast<int64_t>(b.j[i].M) * (b.j[i].NP / 4));
         }
         const unsigned g = static_cast<unsigned>(std::min<int64_t>(cdiv(tot, 256), 8192));
-        ACSC_LAUNCH("sc_split_reduce", pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
+        ACSC_LAUNCH(tag, pass_reduce_kernel, dim3(g, 1, b.count), dim3(256), 0, st, b);
     }
 }
 
-int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits_out)
+int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits_out,
+        const char *red_tag)
 {
     if (reqs.empty())
         return ACSC_OK;
@@ -1349,7 +1350,7 @@ int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t s
                                  static_cast<int>(q.M - r0), NP, 2});
         }
     }
-    add_partials(red, st);
+    add_partials(red_tag, red, st);
     return ACSC_OK;
 }
 
@@ -1423,7 +1424,7 @@ int ema_run(const char *tag, const std::vector<EmaReq> &reqs, float a, float b, 
                                  static_cast<int>(q.m - r0), NP, 2});
         }
     }
-    add_partials(red, st);
+    add_partials("sc_split_reduce", red, st);
     return ACSC_OK;
 }
 

@@ -1889,7 +1889,7 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
                                 RP, m.D.m, m.D.n, RP, m.cw.part});
         }
         launch_tiles("sc_vconvert", t, st);
-        const int rc = pass::run("sc_gv", false, q, st);
+        const int rc = pass::run("sc_gv", false, q, st, nullptr, "sc_gv_reduce");
         if (rc)
             return rc;
     } else {
@@ -1897,7 +1897,7 @@ int correct_group(std::vector<Mat> &ms, int r, float alpha, hipStream_t st, cons
         for (auto &m : ms)
             q.push_back(f32::PassReq{static_cast<const float *>(static_cast<const void *>(m.in->G)), m.D.n, m.in->V, r,
                                      m.cw.Tm, RP, m.D.m, m.D.n, r, RP, m.cw.part, split_count(m.D.m, m.D.n)});
-        if (int rc = f32::pass("sc_gv", false, q, st))
+        if (int rc = f32::pass("sc_gv", false, q, st, nullptr, "sc_gv_reduce"))
             return rc;
     }
     // X = U^T T   [r, RP], and X_f = d X d   [RP, RP], zero-padded

@@ -31,7 +31,8 @@ struct PassReq {
 // Enqueue the products (one NP per call).  With `splits` a product that was
 // cut along k is left in its partials (stride M * NP, row stride NP), as by
 // pass::run; without it C always holds the product.
-int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStream_t st, int *splits = nullptr);
+int pass(const char *tag, bool trans, const std::vector<PassReq> &reqs, hipStream_t st, int *splits = nullptr,
+         const char *red_tag = "sc_split_reduce");
 
 // out = alpha G + (1 - alpha) P V^T with P [m, RP] and V [n, RP] zero-padded to
 // RP (a multiple of 32); with `adam` the blended values are the gradient of

@@ -56,14 +56,16 @@ struct Partials {
     int64_t ldc;
     int M, NP, splits;
 };
-void add_partials(const std::vector<Partials> &red, hipStream_t st);
+void add_partials(const char *tag, const std::vector<Partials> &red, hipStream_t st);
 
 // Enqueue one pass per request (all requests share NP) on `st`.  With
 // `splits` (one entry per request) a product that was cut along k is left as
 // that many partials (partial p at part + p * M * NP, row stride NP) for the
 // next kernel to add in order as it reads them, and C is not written; 1 means
-// that C holds the product.  Without it C always does.
-int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits = nullptr);
+// that C holds the product.  Without it C always does, and the launch that
+// adds the partials is timed as `red_tag`.
+int run(const char *tag, bool trans, const std::vector<Req> &reqs, hipStream_t st, int *splits = nullptr,
+        const char *red_tag = "sc_split_reduce");
 
 // The anchor EMA fused with the first pass of the subspace iteration
 // (Sec. 3.2): M <- a M + b G (the EMA: a = beta, b = 1 - beta; error

@@ -707,6 +707,26 @@ def test_fused_ema_pass_on_ragged_shapes(pk):
                 assert torch.equal(x, y), (arrival, i)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_bench_counts_every_kernel_of_a_correction(pk, dtype):
+    """The benchmark splits a step's kernel time into correction and build by
+    the kernels' names; a G V product that is cut along k (512 x 4096) also
+    launches the addition of its partials, under the correction's own name."""
+    import bench
+    m, n, r = 512, 4096, 16
+    it = dict(G=torch.randn(m, n, device="cuda").to(dtype), ws=pk.workspace(m, n, r, 0, dtype),
+              prior=(torch.randn(m, r, device="cuda"), torch.rand(r, device="cuda"), torch.randn(n, r, device="cuda")),
+              out=torch.empty(m, n, dtype=dtype, device="cuda"))
+    try:
+        pk.acsc_stats_enable(True)
+        pk.sc_correct_batched([it], r, 0.3, dtype=dtype)
+        torch.cuda.synchronize()
+        launches = pk.acsc_stats_read()
+    finally:
+        pk.acsc_stats_enable(False)
+    assert "sc_gv_reduce" in launches and set(launches) <= set(bench.CORRECTION_KERNELS), launches
+
+
 @pytest.mark.parametrize("m,n,count", [(3848, 4200, 9), (4248, 520, 16)])
 def test_narrow_passes_at_two_workgroups_per_cu(pk, m, n, count):
     """Batches of narrow passes whose row blocks fill just over half the CUs
