@@ -495,9 +495,8 @@ def test_who_adds_the_gram_partials(pk, n, k, added):
 
 @pytest.mark.parametrize("dtype,r", [(torch.float32, 8), (torch.bfloat16, 40), (torch.bfloat16, 130)])
 def test_a_nan_gradient_leaves_the_next_build_alone(pk, dtype, r):
-    """A NaN in the anchor gradient spreads into its own prior only: the call
-    returns, and the same workspace then builds a clean matrix's prior to the
-    bits that a fresh one gives."""
+    """A NaN in the anchor gradient: the call returns, and the same workspace
+    then builds a clean matrix's prior to the bits that a fresh one gives."""
     m, n = 300, 400
     g = workloads.gaussian((m, n), seed=2, dtype=dtype).cuda()
     bad = g.clone()
@@ -509,6 +508,31 @@ def test_a_nan_gradient_leaves_the_next_build_alone(pk, dtype, r):
     torch.cuda.synchronize()
     for x, y in zip(again, fresh):
         assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("m,n", [(300, 400), (1500, 400)])
+@pytest.mark.parametrize("dtype,r", [(torch.float32, 8), (torch.bfloat16, 8), (torch.bfloat16, 40), (torch.bfloat16, 130)])
+def test_a_nan_gradient_stays_out_of_its_batch(pk, dtype, r, m, n):
+    """A NaN in one anchor gradient of a batched build spreads into that
+    matrix's prior only: its neighbours (products cut and uncut, Gram
+    partials added by the factorisation and before it) have the bits that
+    the same batch gives with a clean gradient in its place."""
+    gs = [workloads.gaussian((m, n), seed=s, dtype=dtype).cuda() for s in range(3)]
+    bad = gs[1].clone()
+    bad[17, 23] = float("nan")
+    runs = []
+    for mid in (gs[1], bad):
+        items = [dict(G_anc=g, M=torch.zeros(m, n, device="cuda"), ws=pk.workspace(m, n, r, 16, dtype),
+                      out=tuple(torch.zeros(*s, device="cuda") for s in ((m, r), (r,), (n, r), (r,))))
+                 for g in (gs[0], mid, gs[2])]
+        pk.sc_build_prior_batched(items, r, 0.9, 1e-3, 16, 2, seed=3, dtype=dtype)
+        torch.cuda.synchronize()
+        runs.append(items)
+    for i in (0, 2):
+        assert torch.equal(runs[0][i]["M"], runs[1][i]["M"])
+        for x, y in zip(runs[0][i]["out"], runs[1][i]["out"]):
+            assert torch.isfinite(x).all() and torch.equal(x, y)
+    assert torch.isnan(runs[1][1]["M"][17, 23])
 
 
 @pytest.mark.parametrize("r,p", [(16, 8), (130, 16)])
