@@ -115,6 +115,23 @@ def test_phases_equal_the_step_and_project_matches_oracle(pk, dtype):
             assert torch.equal(x[k], y[k]), k
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_phases_equal_the_step_where_products_are_cut(pk, dtype):
+    """The three calls and the one step, bit for bit, on matrices whose two
+    projections are cut along k (P passes through the caller's factor between
+    the calls and stays in the partials of the workspace in the step)."""
+    cases = [_case(700, 4100, 12, 5, dtype), _case(4200, 520, 12, 6, dtype)]
+    a, b = _items(pk, cases, 12, dtype), _items(pk, cases, 12, dtype)
+    pk.psgd_project(a, 12, dtype)
+    pk.psgd_orthogonalize(a, 12, dtype)
+    pk.psgd_decompress(a, 12, dtype)
+    pk.psgd_step(b, 12, dtype)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        for k in ("E", "P", "Q", "out"):
+            assert torch.equal(x[k], y[k]), k
+
+
 @pytest.mark.parametrize("m,n,count", [(4200, 3848, 9), (520, 4248, 16)])
 def test_second_projection_at_two_workgroups_per_cu(pk, m, n, count):
     """Q' = M^T P_hat of batches whose row blocks (over n) fill just over half
