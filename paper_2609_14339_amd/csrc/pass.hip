@@ -2,16 +2,15 @@
 // fp32 accumulation on v_mfma_f32_16x16x32_bf16 (see sc_pass.h).
 //
 // The large operand is the HBM stream; the thin factor is small and is read
-// from L2.  A workgroup owns 256 output rows (four waves of 64) and walks its
-// K range in 64-deep steps.  Each step's slice of the thin factor is staged
-// once in LDS and shared by the four waves; each wave stages its own 64 lines
-// of A (128 contiguous bytes each) in LDS in the order they were loaded and
-// reads its MFMA fragments back from there: 16-byte reads for opA = A,
-// 16-bit gathers for opA = A^T.  Loads run two steps ahead in registers and
-// the LDS tiles are double-buffered: one barrier per step.  Output rows are independent, so the K range is only
-// split (into power-of-two slices, partials summed by a second kernel) when
-// the batch has too few row blocks to give every CU one; block b works on
-// split b % splits, which keeps each split on the same XCDs.
+// from L2.  A workgroup owns 256 output rows and walks its K range in 64-deep
+// steps.  Two kernels: pass_dma_kernel (eight waves, A or A^T, plain or tiled)
+// moves aligned rows and the step's slice of the thin factor straight into a
+// ring of LDS stages; pass_kernel (four waves, A only) takes rows of any
+// alignment through registers.  Output rows are independent, so the K range
+// is only cut where a batch has too few row blocks for the GPU: into pieces of
+// a common length over the batch (choose_splits), whose partials are added in
+// piece order, by the Gram kernel that reads the product next or by
+// pass_reduce_kernel.
 #include "common.h"
 #include "sc_pass.h"
 
@@ -345,8 +344,9 @@ struct SegBatch {
     Seg s[2 * kMaxJobs];
 };
 
-// Eight waves, two per SIMD, one workgroup per CU (the LDS ring takes most of
-// the 160 KiB).  The stage's 256 lines of A form four 64-line groups; wave w
+// Eight waves, two per SIMD.  One workgroup per CU with three stages, whose
+// ring takes most of the 160 KiB of LDS, or, for the launches that two_per_cu()
+// names, two with two stages each (W: waves per SIMD).  The stage's 256 lines of A form four 64-line groups; wave w
 // stages half (w / 4) of group (w % 4), 32 lines, and multiplies the 32
 // output rows of that half against all NP columns.  For opA = A those are
 // the lines it staged itself; for opA = A^T it also reads the other half's
@@ -360,8 +360,6 @@ struct SegBatch {
 // the MFMA's power draw, not HBM, sets their pace: covering 144 columns with
 // 16-wide tiles (rather than padding to 160 for 32x32 tiles) takes 8% less
 // time, and needs fewer fragment reads than 32x32 tiles plus a 16-wide one.
-// One workgroup per CU with three stages, or, for the launches that two_per_cu()
-// names, two with two stages each (W: waves per SIMD).
 template <bool TRANS, int NT, int S, int W>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W, W))) void pass_dma_kernel(const SegBatch sb,
                                                                                                   int np)
@@ -1128,11 +1126,11 @@ void ema_launch(const char *tag, const EmaBatch &b, int grid, int np, float a, f
 }
 
 // k pieces per row block for a batch whose row blocks do not fill the GPU.
-// A CU takes one pass workgroup (narrow ones: up to two), so the pass takes as long as the CU with the
-// most steps: a common piece length serves a batch that mixes row lengths
-// better than one split count for every job (with 2048- and 8192-deep rows
-// cut in four, the CUs of the long rows work four times as long as the
-// others).  The lengths between "one round of equal pieces" and whole rows
+// A CU takes one pass workgroup (or two narrow ones), so the pass takes as long
+// as the CU with the most steps: a common piece length serves a batch that
+// mixes row lengths better than one split count for every job (with 2048- and
+// 8192-deep rows cut in four, the CUs of the long rows work four times as long
+// as the others).  The lengths between "one round of equal pieces" and whole rows
 // are tried on the simulated dispatch; a piece costs kPieceOver steps more
 // for its empty pipeline and np / 32 for the partial it stores (a step is 32
 // KiB of the stream per CU).  Measured on the six matrices of a 1B-class

@@ -989,18 +989,16 @@ __global__ __launch_bounds__(256) void jacobi_blocks_kernel(const Batch<JacJob> 
 // Elementwise kernels.
 // ---------------------------------------------------------------------------
 // M <- beta * M + (1 - beta) * G  (fp32 state)
-template <typename GT>
 struct Ema32Job {
     float *M;
-    const GT *G;
+    const float *G;
     int64_t count;
 };
 
-template <typename GT>
-__global__ __launch_bounds__(256) void ema_kernel(const Batch<Ema32Job<GT>> jb, float beta, float omb)
+__global__ __launch_bounds__(256) void ema_kernel(const Batch<Ema32Job> jb, float beta, float omb)
 {
     float *M = jb.j[blockIdx.z].M;
-    const GT *G = jb.j[blockIdx.z].G;
+    const float *G = jb.j[blockIdx.z].G;
     const int64_t count = jb.j[blockIdx.z].count;
     if (!G)
         return;
@@ -1009,28 +1007,15 @@ __global__ __launch_bounds__(256) void ema_kernel(const Batch<Ema32Job<GT>> jb, 
          i += stride) {
         if (i + 4 <= count) {
             float4 m = *reinterpret_cast<const float4 *>(M + i);
-            float g0, g1, g2, g3;
-            if constexpr (sizeof(GT) == 2) {
-                const uint2 gb = *reinterpret_cast<const uint2 *>(G + i);
-                g0 = __uint_as_float(gb.x << 16);
-                g1 = __uint_as_float(gb.x & 0xFFFF0000u);
-                g2 = __uint_as_float(gb.y << 16);
-                g3 = __uint_as_float(gb.y & 0xFFFF0000u);
-            } else {
-                const float4 gv = *reinterpret_cast<const float4 *>(G + i);
-                g0 = gv.x;
-                g1 = gv.y;
-                g2 = gv.z;
-                g3 = gv.w;
-            }
-            m.x = ema_step(m.x, g0, beta, omb);
-            m.y = ema_step(m.y, g1, beta, omb);
-            m.z = ema_step(m.z, g2, beta, omb);
-            m.w = ema_step(m.w, g3, beta, omb);
+            const float4 g = *reinterpret_cast<const float4 *>(G + i);
+            m.x = ema_step(m.x, g.x, beta, omb);
+            m.y = ema_step(m.y, g.y, beta, omb);
+            m.z = ema_step(m.z, g.z, beta, omb);
+            m.w = ema_step(m.w, g.w, beta, omb);
             *reinterpret_cast<float4 *>(M + i) = m;
         } else {
             for (int64_t j = i; j < count; ++j)
-                M[j] = ema_step(M[j], to_f32<GT>(G[j]), beta, omb);
+                M[j] = ema_step(M[j], G[j], beta, omb);
         }
     }
 }
@@ -1720,18 +1705,18 @@ int build_group(std::vector<Mat> &ms, acsc_dtype dt, float beta, int r, int powe
             }
             launch_jobs("sc_ema", ema_shadow_kernel, j, dim3(grid1d(tot)), dim3(256), 0, st, beta, omb);
         } else {
-            std::vector<Ema32Job<float>> j;
+            std::vector<Ema32Job> j;
             int64_t tot = 1;
             for (auto &m : ms) {
                 const int64_t c = static_cast<int64_t>(m.D.m) * m.D.n;
-                j.push_back(Ema32Job<float>{m.in->M, static_cast<const float *>(m.in->G), c});
+                j.push_back(Ema32Job{m.in->M, static_cast<const float *>(m.in->G), c});
                 tot = std::max(tot, cdiv(c, 4));
             }
             bool any = false;
             for (auto &m : ms)
                 any = any || m.in->G;
             if (any)
-                launch_jobs("sc_ema", ema_kernel<float>, j, dim3(grid1d(tot)), dim3(256), 0, st, beta, omb);
+                launch_jobs("sc_ema", ema_kernel, j, dim3(grid1d(tot)), dim3(256), 0, st, beta, omb);
         }
     }
     if (phases & kPhaseSubspace) {
@@ -2098,20 +2083,20 @@ int psgd_project_phase(std::vector<PsgdItem> &it, bool use16, int r, std::vector
         }
     } else {
         std::vector<PadJob<float>> pj;
-        std::vector<Ema32Job<float>> ej;
+        std::vector<Ema32Job> ej;
         std::vector<f32::PassReq> q;
         int64_t tp = 1, te = 1;
         for (auto &x : it) {
             pj.push_back(PadJob<float>{x.in->Q, x.in->n, x.w.pw.Z});
             tp = std::max<int64_t>(tp, static_cast<int64_t>(x.in->n) * KP);
             const int64_t c = static_cast<int64_t>(x.in->m) * x.in->n;
-            ej.push_back(Ema32Job<float>{x.in->E, static_cast<const float *>(x.in->G), c});
+            ej.push_back(Ema32Job{x.in->E, static_cast<const float *>(x.in->G), c});
             te = std::max(te, cdiv(c, 4));
             q.push_back(f32::PassReq{x.in->E, x.in->n, x.w.pw.Z, KP, x.w.pw.Y, KP, x.in->m, x.in->n, r, KP,
                                      x.w.pw.part, split_count(x.in->m, x.in->n)});
         }
         launch_jobs("psgd_qconvert", pad_convert_kernel<float>, pj, dim3(grid1d(tp)), dim3(256), 0, st, r, KP);
-        launch_jobs("psgd_feedback", ema_kernel<float>, ej, dim3(grid1d(te)), dim3(256), 0, st, 1.0f, 1.0f);
+        launch_jobs("psgd_feedback", ema_kernel, ej, dim3(grid1d(te)), dim3(256), 0, st, 1.0f, 1.0f);
         if (int rc = f32::pass("psgd_pass_mq", false, q, st, splits.data()))
             return rc;
     }

@@ -6,9 +6,9 @@ the oracle forms G_proj, the global norm, the clip and the AdamW step in
 float64.  Compared: the weight update W_new - W_old, the moments and the
 reported norm, by relative Frobenius error: 1e-4 for fp32 gradients, 2e-2
 for bf16 gradients (fp32 accumulation), as for the correction itself.  The
-cases cover every kernel path: fp32 (64 x 64 tiles), bf16 with a padded rank
-the streamed-tile kernel does not take, the streamed-tile kernel with 16-byte
-and with only 4-byte aligned state, more than 16 matrices in one call (the
+cases cover every kernel path: fp32, bf16 (the streamed-tile kernel) at small
+and large padded ranks, with 16-byte and with only 4-byte aligned state and
+with rows of odd width, more than 16 matrices in one call (the
 norm accumulated over launches), and a full-size 70B-class layer on sampled
 rows.
 """
@@ -102,7 +102,8 @@ def test_fp32_matches_oracle(pk, t, max_norm):
 
 @pytest.mark.parametrize("m,n,r", [(300, 200, 7), (129, 4104, 40), (1000, 17, 3)])
 def test_bf16_padded_ranks_off_the_tile_kernel(pk, m, n, r):
-    # padded ranks 32 and 64 / unaligned rows: the 128 x 128 tile kernel
+    # padded ranks 32 and 64, rows of 17 and 4104 entries (the name is from when
+    # these ranks had a kernel of their own; the streamed-tile kernel has them now)
     cases = [_case(m, n, r, 10 + r, torch.bfloat16, 5)]
     got, N = _run(pk, cases, r, 0.3, 5, 0.5, torch.bfloat16)
     ref, No = _oracle(cases, 0.3, 5, 0.5)

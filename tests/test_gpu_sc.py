@@ -83,9 +83,10 @@ def test_correct_ragged_shapes(pk, dtype, m, n, r):
 @pytest.mark.parametrize("m,n,r", [(130, 260, 64), (257, 1003, 50), (129, 515, 128), (200, 333, 190), (300, 1001, 24),
                                    (140, 452, 80), (1000, 4099, 150), (4097, 1101, 73), (513, 2049, 160)])
 def test_correct_stores_widths_that_are_no_multiple_of_8(pk, m, n, r):
-    """bf16 rows that are not 16-byte aligned take the element-wise stores of
-    the blend at every padded rank; the output starts as NaN, so an element
-    that is not stored shows."""
+    """bf16 rows that are not 16-byte aligned, at every padded rank: whole
+    chunks take unaligned 16-byte stores and each row's last chunk
+    element-wise ones; the output starts as NaN, so an element that is not
+    stored shows."""
     U, s, V = workloads.random_orthonormal_basis(m, n, r, seed=m + n + r)
     G = (((U * 0.5) @ V.T) + 0.02 * workloads.gaussian((m, n), seed=4).double()).to(torch.bfloat16)
     d = osp.filter_weights(s.numpy(), 0.7)
