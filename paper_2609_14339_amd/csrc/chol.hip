@@ -356,10 +356,10 @@ int prepare(int KP)
 {
     if (!supported(KP))
         return set_error(ACSC_EINVAL, "chol: padded order %d not handled", KP);
-    int rc = allow_lds(chol_blocked_kernel<true, false>, lds_bytes(KP));
-    rc = rc ? rc : allow_lds(chol_blocked_kernel<true, true>, lds_bytes(KP));
-    rc = rc ? rc : allow_lds(chol_blocked_kernel<false, false>, lds_bytes(KP));
-    return rc ? rc : allow_lds(chol_blocked_kernel<false, true>, lds_bytes(KP));
+    // (orders that add partials need no more LDS than every kernel may have)
+    static_assert(adds_partials(48, 1) && !adds_partials(64, 1), "orders that add partials");
+    const int rc = allow_lds(chol_blocked_kernel<true, false>, lds_bytes(KP));
+    return rc ? rc : allow_lds(chol_blocked_kernel<false, false>, lds_bytes(KP));
 }
 
 int run(const char *tag, const std::vector<Req> &reqs, int k, int KP, bool invert, hipStream_t st)

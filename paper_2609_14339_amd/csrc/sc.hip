@@ -491,7 +491,13 @@ __device__ __forceinline__ void rotation(double al, double be, double ga, double
 // within a block go before the first of a sweep, together with the exact
 // squared norms, which the rotations then update.
 // Measured (six 48 x 48, four 80 x 80 factors): 190 and 400 us with a barrier
-// and an LDS round trip per round, 145 and 310 us so.
+// and an LDS round trip per round, 145 and 310 us so; one factor of a 1024 x 1024
+// matrix, from a random start: 46 and 43 us at k = 16, 69 and 59 at 24, 95 and
+// 74 at 32, 409 and 174 at 64, 723 and 396 at 96, 872 and 517 at 112, 4077
+// and 759 at 128.  Warm-started, also with no new gradient, where the
+// form before could leave out the pairs that were orthogonal already: 46 and
+// 43, 72 and 58, 93 and 74, 311 and 174, 544 and 336, 615 and 441, 2642 and
+// 545.  Sweeps: 6 to 8 then, one fewer now (the inner-product check).
 // ---------------------------------------------------------------------------
 struct JacJob {
     const double *Lf;

@@ -36,7 +36,7 @@ struct Req {
 // 187 and 195 us; KP = 32, 8 partials 248 and 255 (16: 260 both); KP = 48,
 // 8 partials 374 and 382, 12 partials 378 and 366; KP = 64, 4 partials 472
 // and 463; KP = 144, 16 partials 1709 and 1528.
-inline bool adds_partials(int KP, int blocks)
+constexpr bool adds_partials(int KP, int blocks)
 {
     return KP <= 48 && blocks <= 16 && blocks * KP * KP * 8 <= 144 * 1024;
 }
