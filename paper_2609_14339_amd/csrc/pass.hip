@@ -825,6 +825,8 @@ SegPlan plan(const std::vector<JobShape> &js, int per_cu)
         }
     }
     std::lock_guard<std::mutex> g(mu);
+    if (cache.size() >= 1024)
+        cache.clear();
     cache.emplace(key, best);
     return best;
 }
